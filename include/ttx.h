@@ -457,16 +457,18 @@ ttx_status ttx_gemm_panels(ttx_dtype dtype, int panel, int64_t m, int64_t n, int
  * TTX_EINVAL, and so are extents that differ for one label.  na, nb, nc
  * are in 0..TTX_MAX_DIMS (0: a scalar).
  *
- * Execution: each operand that is not already a matrix (its free modes and
- * its contracted modes in two contiguous blocks, in either order, with the
- * contracted modes in the order the other operand uses) is transposed into
- * one (ttx_plan_execute); both are packed into matrix-core panels
- * (ttx_pack, TTX_PACK_MFMA_A or _B, whichever reads the matrix in its
- * storage order); ttx_gemm_panels forms the m x n product; and one
- * transposition writes alpha * product + beta * C into C's mode order
- * (Eqn. 1, so beta == 0 never reads C).  The product is summed in the
- * element type by the matrix cores (see ttx_gemm_panels); alpha and beta
- * are applied once, in the last step.  dtype TTX_F32 or TTX_F64 (else
+ * The matrix form (ttx_contraction_describe): each operand that is not
+ * already a matrix (its free modes and its contracted modes in two contiguous
+ * blocks, in either order, with the contracted modes in the order the other
+ * operand uses) is transposed into one, both are packed into matrix-core
+ * panels (TTX_PACK_MFMA_A or _B, whichever reads the matrix in its storage
+ * order), and the m x n product is transposed into C's mode order with alpha
+ * and beta (Eqn. 1, so beta == 0 never reads C).  Execution folds these
+ * transpositions into the addresses of one kernel, which reads the operands
+ * and writes C where they lie; sums that are cut over workgroups and operands
+ * that many tiles share pass through the workspace.  The product is summed
+ * in the element type by the matrix cores (see ttx_gemm_panels); alpha and
+ * beta are applied once, at the end.  dtype TTX_F32 or TTX_F64 (else
  * TTX_EUNSUPPORTED).
  *
  * The plan holds host memory only (no HIP call at creation).  Execution
@@ -481,7 +483,7 @@ typedef struct ttx_contraction ttx_contraction;
 typedef struct ttx_contraction_info {
     int64_t m, n, k;            /* the matrix product's extents */
     int panel;                  /* matrix-core panel (16 or 32) */
-    int transposed_a;           /* 1: A is transposed into matrix order before packing */
+    int transposed_a;           /* 1: the matrix form transposes A into matrix order */
     int transposed_b;
     int pack_kind_a;            /* TTX_PACK_MFMA_A or TTX_PACK_MFMA_B (A stored contracted-major) */
     int pack_kind_b;            /* TTX_PACK_MFMA_B, or TTX_PACK_MFMA_A (B stored free-major) */

