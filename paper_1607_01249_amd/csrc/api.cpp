@@ -7,6 +7,7 @@
 #include <string>
 #include <unordered_map>
 
+#include "box.h"
 #include "ttx_internal.h"
 
 // What a plan runs for one beta class: the configuration and, when one is
@@ -18,10 +19,12 @@ struct PlanExec {
     ttx_config cfg;
     int from_table;
     const ttx::JitKernel* jit;   // owned by the JIT cache (lives until the process ends)
+    std::shared_ptr<const ttx::BoxPlan> box;   // box tiles, run in place of cfg
 };
 
 struct ttx_plan {
     ttx::Problem prob;
+    bool per_call = false;                     // of the per-call entry points (may run box tiles)
     std::shared_ptr<const PlanExec> exec[2];   // [beta_is_zero]; read and replaced with std::atomic_load/store
     std::mutex mu;                             // serialises the writers
     bool user_set[2] = {false, false};
@@ -30,8 +33,9 @@ struct ttx_plan {
     bool jit_tried[2] = {false, false};        // automatic specialisation attempted
 
     std::shared_ptr<const PlanExec> load(int z) const { return std::atomic_load(&exec[z]); }
-    void publish(int z, const ttx_config& cfg, int from_table, const ttx::JitKernel* jit) {
-        std::atomic_store(&exec[z], std::shared_ptr<const PlanExec>(new PlanExec{cfg, from_table, jit}));
+    void publish(int z, const ttx_config& cfg, int from_table, const ttx::JitKernel* jit,
+                 std::shared_ptr<const ttx::BoxPlan> box = nullptr) {
+        std::atomic_store(&exec[z], std::shared_ptr<const PlanExec>(new PlanExec{cfg, from_table, jit, std::move(box)}));
     }
 };
 
@@ -46,6 +50,18 @@ ttx_status fail(ttx_status s, const std::string& msg) {
 
 void clear_error() { g_last_error.clear(); }
 
+// A per-call plan runs box tiles wherever the problem has a box and the tune
+// table has no entry for it: over 364 drawn problems (4 KB to 650 MB, all
+// types, leading dimensions) they take 6.30 ms where the menu's heuristic
+// configurations take 7.93 ms, and 6.28 ms is the sum of the better of the two;
+// the menu is ahead by more than 1 us only on problems below 15 MB whose
+// kernels take 4 to 7 us.  Plans of ttx_plan_create run the configuration
+// that they describe.
+static std::shared_ptr<const BoxPlan> choose_box(const Problem& p, bool beta0) {
+    auto bp = std::make_shared<BoxPlan>();
+    return plan_box(p, beta0, bp.get()) ? bp : nullptr;
+}
+
 static void resolve_configs(ttx_plan* plan) {
     plan->table_gen = table_generation();
     for (int z = 0; z < 2; ++z) {
@@ -54,18 +70,20 @@ static void resolve_configs(ttx_plan* plan) {
         if (table_lookup(plan->prob, z == 1, &c))
             plan->publish(z, c, 1, nullptr);
         else
-            plan->publish(z, default_config(plan->prob), 0, nullptr);
+            plan->publish(z, default_config(plan->prob), 0, nullptr,
+                          plan->per_call ? choose_box(plan->prob, z == 1) : nullptr);
     }
 }
 
 static ttx_status new_plan(ttx_plan** out, int dtype, int n, const int* perm, const int64_t* size,
-                           const int64_t* outer_a, const int64_t* outer_b) {
+                           const int64_t* outer_a, const int64_t* outer_b, bool per_call) {
     Problem p;
     ttx_status st = make_problem(dtype, n, perm, size, outer_a, outer_b, &p);
     if (st != TTX_OK) return st;
     ttx_plan* plan = new (std::nothrow) ttx_plan();
     if (!plan) return fail(TTX_ENOMEM, "out of host memory");
     plan->prob = p;
+    plan->per_call = per_call;
     resolve_configs(plan);
     *out = plan;
     return TTX_OK;
@@ -114,7 +132,9 @@ static ttx_status execute(const ttx_plan* plan, const Scalar& alpha, const void*
             return TTX_OK;
         }
     }
-    hipError_t e = launch_tiles(p, x->cfg, beta0, A, beta0 ? nullptr : Bin, Bout, alpha, beta, stream);
+    const void* Bsrc = beta0 ? nullptr : Bin;
+    const hipError_t e = x->box ? launch_box(p, *x->box, beta0, A, Bsrc, Bout, alpha, beta, stream)
+                                : launch_tiles(p, x->cfg, beta0, A, Bsrc, Bout, alpha, beta, stream);
     if (e != hipSuccess) return fail(TTX_EHIP, std::string("kernel launch: ") + hipGetErrorString(e));
     return TTX_OK;
 }
@@ -193,7 +213,7 @@ ttx_status transpose_cached(int dtype, int n, const int* perm, const int64_t* si
     }
     if (!plan || plan->table_gen != table_generation()) {
         ttx_plan* raw = nullptr;
-        ttx_status st = new_plan(&raw, dtype, n, perm, size, outer_a, outer_b);
+        ttx_status st = new_plan(&raw, dtype, n, perm, size, outer_a, outer_b, true);
         if (st != TTX_OK) return st;
         plan.reset(raw);
         std::lock_guard<std::mutex> lock(g_cache_mu);
@@ -241,7 +261,7 @@ const char* ttx_version(void) { return "ttx 0.1 gfx950"; }
 ttx_status ttx_plan_create(ttx_plan** plan, ttx_dtype dtype, int n, const int* perm,
                            const int64_t* size, const int64_t* outer_a, const int64_t* outer_b) {
     if (!plan) return fail(TTX_EINVAL, "plan must not be NULL");
-    return new_plan(plan, dtype, n, perm, size, outer_a, outer_b);
+    return new_plan(plan, dtype, n, perm, size, outer_a, outer_b, false);
 }
 
 ttx_status ttx_plan_execute(const ttx_plan* plan, double alpha, const void* A, double beta, void* B,
@@ -328,7 +348,7 @@ ttx_status ttx_plan_specialise(ttx_plan* plan, int beta_is_zero, int reps, int* 
         generic_from_table = table_lookup(plan->prob, z == 1, &c) ? 1 : 0;
         generic = generic_from_table ? c : default_config(plan->prob);
     }
-    plan->publish(z, generic, generic_from_table, nullptr);
+    plan->publish(z, generic, generic_from_table, nullptr, generic_from_table ? nullptr : prev->box);
     if (plan->prob.family != TTX_FAMILY_MOVED && plan->prob.family != TTX_FAMILY_PRESERVED) return TTX_OK;
     // a configuration tuned for specialised execution, when the table has one
     // and the caller has not set the config

@@ -1,0 +1,333 @@
+// Choice of a box tile (host only; see box.h).  Every pair of candidate runs
+// gives a box, small ones also filled up by a third index; the cheapest by an
+// estimate of its time is taken (40 to 60 us of host time for a new problem).
+#include <algorithm>
+#include <cmath>
+#include <cstring>
+
+#include "box.h"
+#include "ttx_internal.h"
+
+namespace ttx {
+namespace {
+
+constexpr int kBoxBytes = 16384;
+
+// One side's run: its first `whole` indices and `t` steps of the next one.
+struct Run {
+    int whole;
+    int64_t t;       // 1 .. extent - 1, or 0: no split index
+    int64_t len;
+};
+
+// Candidate runs of about 64 bytes to 4 KiB along `order` (A's or B's): their
+// whole indices, and pieces of the next one (whole 128-byte lines of a long
+// stride-1 index, else near-even pieces).  A run that can't go on because the
+// next index doesn't follow in memory may be shorter.
+int runs_of(const Problem& p, const int* order, bool in_a, int es, Run* out, int cap) {
+    int n = 0;
+    int64_t len = 1;
+    const int64_t most = kBoxBytes / es, line = 128 / es;
+    auto follows = [&](int k) {
+        if (k >= p.n) return false;
+        const Dim &d = p.dim[order[k]], &e = p.dim[order[k - 1]];
+        return in_a ? d.sa == e.sa * e.size : d.sb == e.sb * e.size;
+    };
+    for (int k = 0; n < cap && (k == 0 || follows(k)); ++k) {
+        const Dim& d = p.dim[order[k]];
+        int64_t last = 0;
+        for (int64_t want = 64; want <= 4096 && n < cap; want *= 2) {
+            int64_t t = std::max<int64_t>(1, want / es / len);
+            if (t >= d.size || len * t > most) break;
+            const int64_t pieces = (d.size + t - 1) / t;
+            if (len != 1 || t % line || d.size < 4 * t) t = (d.size + pieces - 1) / pieces;
+            if (t == last || t >= d.size) continue;
+            last = t;
+            out[n++] = Run{k, t, len * t};
+        }
+        if (len * d.size > most) break;
+        len *= d.size;
+        if ((len * es >= 64 || !follows(k + 1)) && n < cap) out[n++] = Run{k + 1, 0, len};
+        if (len * es >= 4096) break;
+    }
+    return n;
+}
+
+// One box: its extents t (by index), the runs they give and what they cost.
+struct Box {
+    int64_t t[kMaxDims];
+    int64_t volume, LA, LB;      // elements of the box and of its runs
+    int sa, sb, sc;              // indices that the runs cut, and a third one that the box cuts, -1: none
+    int in_run_a, in_run_b;      // positions (A's order, B's order) that a run holds
+    int64_t nua, nub;            // units of a full box
+    double tiles;
+};
+
+// Fills in a box from its extents; false where the kernel can't take it.
+bool box_of(const Problem& p, Box* b) {
+    const int ea = elem_bytes(p.dtype_a), eb = elem_bytes(p.dtype);
+    const int UA = 16 / ea, UB = 16 / eb;
+    const int64_t* t = b->t;
+    int dims = 0;
+    b->volume = 1;
+    b->tiles = 1;
+    for (int d = 0; d < p.n; ++d) {
+        b->volume *= t[d];
+        dims += t[d] > 1;
+        b->tiles *= double((p.dim[d].size + t[d] - 1) / t[d]);
+    }
+    if (dims > kBoxDims || b->volume * eb > kBoxBytes || b->volume * ea > 2 * kBoxBytes) return false;
+    // a run: whole indices that follow each other in memory, and part of the next
+    b->LA = b->LB = 1;
+    b->sa = b->sb = -1;
+    b->in_run_a = b->in_run_b = 0;
+    for (int k = 0; k < p.n; ++k) {
+        if (k > 0 && p.dim[k].sa != p.dim[k - 1].sa * p.dim[k - 1].size) break;
+        b->LA *= t[k];
+        b->in_run_a = k + 1;
+        if (t[k] < p.dim[k].size) {
+            b->sa = k;
+            break;
+        }
+    }
+    for (int k = 0; k < p.n; ++k) {
+        const int d = p.perm[k];
+        if (k > 0 && p.dim[d].sb != p.dim[p.perm[k - 1]].sb * p.dim[p.perm[k - 1]].size) break;
+        b->LB *= t[d];
+        b->in_run_b = k + 1;
+        if (t[d] < p.dim[d].size) {
+            b->sb = d;
+            break;
+        }
+    }
+    if (b->LA < UA || b->LB < UB) return false;
+    // of the indices outside the runs one may be cut
+    b->sc = -1;
+    for (int d = 0; d < p.n; ++d)
+        if (t[d] > 1 && t[d] < p.dim[d].size && d != b->sa && d != b->sb) {
+            if (b->sc >= 0) return false;
+            b->sc = d;
+        }
+    b->nua = b->volume / b->LA * ((b->LA + UA - 1) / UA);
+    b->nub = b->volume / b->LB * ((b->LB + UB - 1) / UB);
+    if (b->nua > kThreads * kBoxUnits || b->nub > kThreads * kBoxUnits) return false;
+    return b->volume / b->LA * (b->LA + 2 * UA) <= (kBoxBytes + 4096) / eb;
+}
+
+// Whether two units per thread hold the box.
+bool small_box(const Problem& p, const Box& b) {
+    const int UA = 16 / elem_bytes(p.dtype_a);
+    return b.nua <= 2 * kThreads && b.nub <= 2 * kThreads &&
+           b.volume / b.LA * (b.LA + 2 * UA) <= (8192 + 2048) / elem_bytes(p.dtype);
+}
+
+// Estimated time in microseconds: the bytes at the rate of a large copy; per
+// run that does not end where the next box of B's order goes on, about half a
+// line; a few bytes per unit (addresses, LDS) and a fixed cost per box; and
+// what one compute unit's boxes wait for, which counts where there are few.
+// The constants are fitted to the times of some 9000 boxes of 175 problems.
+double box_cost(const Problem& p, bool beta0, const Box& b) {
+    const int ea = elem_bytes(p.dtype_a), eb = elem_bytes(p.dtype);
+    const double n = double(p.elements), sides = beta0 ? 1.0 : 2.0;   // accesses of B
+    // boxes between one box and the one that goes on with its run of A or B
+    double da = 1.0, db = 1.0;
+    for (int k = 0, d; k < p.n && (d = p.perm[k]) != b.sa; ++k) da *= double((p.dim[d].size + b.t[d] - 1) / b.t[d]);
+    for (int k = 0, d; k < p.n && (d = p.perm[k]) != b.sb; ++k) db *= double((p.dim[d].size + b.t[d] - 1) / b.t[d]);
+    const double runs_a = n / double(b.LA) * (b.sa >= 0 && da <= 8.0 ? 25.0 : 50.0);
+    const double runs_b = n / double(b.LB) * (b.sb >= 0 && db <= 8.0 ? 22.0 : 54.0) * sides;
+    const double units = 2.8 * double(b.nua + b.nub) * b.tiles;
+    const double wide = small_box(p, b) ? 1.0 : beta0 ? 1.037 : 1.066;
+    const double bytes = (n * (ea + eb * sides) + runs_a + runs_b + units) * wide + 1500.0 * b.tiles;
+    const double rounds = std::ceil(b.tiles / 256.0), fill = std::ceil(double(std::max(b.nua, b.nub)) / kThreads);
+    return bytes / 6e6 + 0.052 * fill * (1.0 + 0.025 * (rounds - 1.0));
+}
+
+template <typename F>
+void each_box(const Problem& p, F&& f) {
+    const int ea = elem_bytes(p.dtype_a), eb = elem_bytes(p.dtype);
+    int id[kMaxDims];
+    for (int d = 0; d < p.n; ++d) id[d] = d;
+    Run ra[24], rb[24];
+    const int na = runs_of(p, id, true, ea, ra, 24), nb = runs_of(p, p.perm, false, eb, rb, 24);
+    for (int i = 0; i < na; ++i)
+        for (int j = 0; j < nb; ++j) {
+            Box b;
+            for (int d = 0; d < p.n; ++d) b.t[d] = 1;
+            for (int k = 0; k < ra[i].whole; ++k) b.t[k] = p.dim[k].size;
+            if (ra[i].t) b.t[ra[i].whole] = ra[i].t;
+            for (int k = 0; k < rb[j].whole; ++k) b.t[p.perm[k]] = p.dim[p.perm[k]].size;
+            if (rb[j].t) b.t[p.perm[rb[j].whole]] = std::max(b.t[p.perm[rb[j].whole]], rb[j].t);
+            if (!box_of(p, &b)) continue;
+            f(b);
+            // a small box filled up: with the next index of A's order or of B's,
+            // to two or to four units a thread
+            const int64_t units = std::max(b.nua, b.nub);
+            for (int side = 0; side < 2 && units <= kThreads; ++side) {
+                int d = -1;
+                for (int k = 0; k < p.n && d < 0; ++k) {
+                    const int x = side ? p.perm[k] : k;
+                    if (b.t[x] == 1 && x != b.sa && x != b.sb) d = x;
+                }
+                if (d < 0) continue;
+                for (int64_t most = 2 * kThreads; most <= 4 * kThreads; most *= 2) {
+                    Box c = b;
+                    const int64_t steps = std::min(p.dim[d].size, most / units);
+                    const int64_t pieces = (p.dim[d].size + steps - 1) / steps;
+                    c.t[d] = (p.dim[d].size + pieces - 1) / pieces;
+                    if (c.t[d] > 1 && box_of(p, &c)) f(c);
+                    if (c.t[d] == p.dim[d].size) break;
+                }
+            }
+        }
+}
+
+// LDS cycles of one wavefront's first units (put and gather) in a full box: a
+// bank serves one word a cycle, 32 words in all.
+template <int UA, int UB>
+int bank_cycles(const BoxShape& s, int elem) {
+    const int words = elem / 4, group = 32 / words;   // lanes served together
+    const BoxCoord c{0, 0, s.tA, s.tB, s.tC};
+    int cycles = 0, at[64][UA + UB];
+    for (int lane = 0; lane < 64; ++lane) {
+        BoxUnits<UA, UB, 1> u;
+        u.init(s, lane, c);
+        for (int j = 0; j < UA; ++j) at[lane][j] = u.put(0, j) + (u.put(0, j) >> s.skew);
+        for (int j = 0; j < UB; ++j) at[lane][UA + j] = u.gather(0, j);
+    }
+    for (int j = 0; j < UA + UB; ++j) {
+        if (s.aligned && j < UA) continue;   // written in whole units
+        for (int g = 0; g < 64; g += group) {
+            int seen[32][32], n[32] = {}, most = 1;
+            for (int lane = g; lane < g + group; ++lane) {
+                const int bank = at[lane][j] * words % 32;
+                bool again = false;   // the same element: one access
+                for (int k = 0; k < n[bank]; ++k) again |= seen[bank][k] == at[lane][j];
+                if (!again) seen[bank][n[bank]++] = at[lane][j];
+                most = std::max(most, n[bank]);
+            }
+            cycles += most;
+        }
+    }
+    return s.aligned ? cycles + 8 : cycles;
+}
+
+int bank_cycles(const Problem& p, const BoxShape& s) {
+    const int ea = elem_bytes(p.dtype_a), eb = elem_bytes(p.dtype);
+    if (ea == eb) return eb == 4 ? bank_cycles<4, 4>(s, 4) : eb == 8 ? bank_cycles<2, 2>(s, 8) : bank_cycles<1, 1>(s, 16);
+    if (ea < eb) return eb == 8 ? bank_cycles<4, 2>(s, 8) : bank_cycles<2, 1>(s, 16);
+    return eb == 4 ? bank_cycles<2, 4>(s, 4) : bank_cycles<1, 2>(s, 8);
+}
+
+// The LDS layout: A's runs one after the other, with the distance between them
+// (whole units, or an odd number of elements) and the skew that cost the
+// fewest cycles; false if none fits into `cap` elements.
+bool place(const Problem& p, const Box& b, int cap, BoxShape* s) {
+    const int UA = 16 / elem_bytes(p.dtype_a), eb = elem_bytes(p.dtype);
+    const int shift = eb == 4 ? 5 : eb == 8 ? 4 : 3;
+    int best = 1 << 30;
+    BoxShape chosen = *s;
+    for (int option = 0; option < 4; ++option) {
+        const bool units = option == 0;
+        if (units && b.LA % UA) continue;
+        const int64_t odd = units ? UA : 1;
+        const int64_t pitch = option == 2 ? b.LA : (b.LA / odd) % 2 ? b.LA : b.LA + odd;
+        s->aligned = units && elem_bytes(p.dtype_a) == eb;
+        s->skew = option < 2 ? 31 : shift;
+        int64_t ls[kMaxDims], at = 1;
+        for (int d = 0; d < p.n; ++d) {
+            if (d == b.in_run_a) at = pitch;
+            ls[d] = at;
+            at *= b.t[d];
+        }
+        for (int k = 0, d = 0; d < p.n; ++d)
+            if (b.t[d] > 1 || d == b.sa || d == b.sb) s->dA[k++].ls = int(ls[d]);
+        for (int k = 0, q = 0; q < p.n; ++q) {
+            const int d = p.perm[q];
+            if (b.t[d] > 1 || d == b.sa || d == b.sb) s->dB[k++].ls = int(ls[d]);
+        }
+        const int64_t last = b.volume / b.LA * pitch + UA;
+        if (last + (last >> s->skew) > cap) continue;
+        // a skew costs instructions too
+        const int cycles = bank_cycles(p, *s) + (option < 2 ? 0 : 24);
+        if (cycles < best) best = cycles, chosen = *s;
+    }
+    *s = chosen;
+    return best < (1 << 30);
+}
+
+bool make_box(const Problem& p, bool beta0, const Box& b, BoxPlan* out) {
+    const int UA = 16 / elem_bytes(p.dtype_a);
+    const int64_t* t = b.t;
+    const int64_t LA = b.LA, LB = b.LB;
+    const int sa = b.sa, sb = b.sb, in_run_a = b.in_run_a, in_run_b = b.in_run_b;
+    BoxShape& s = out->s;
+    std::memset(&s, 0, sizeof(s));
+    out->cost = box_cost(p, beta0, b);
+    out->elements = b.volume;
+    out->units = small_box(p, b) ? 2 : 4;
+    s.tA = sa >= 0 ? int(t[sa]) : 1;
+    s.tB = sb >= 0 ? int(t[sb]) : 1;
+    s.tC = b.sc >= 0 ? int(t[b.sc]) : 1;
+    s.wA = int(LA / s.tA);
+    s.wB = int(LB / s.tB);
+    auto put = [&](BoxDim* dims, int* n, int d) {
+        BoxDim& x = dims[(*n)++];
+        x.ext = int(t[d]);
+        x.split = (d == sa ? 1 : 0) | (d == sb ? 2 : 0) | (d == b.sc ? 4 : 0);
+        x.sa = int(p.dim[d].sa);
+        x.sb = int(p.dim[d].sb);
+    };
+    s.skew = 31;
+    // a split index stays listed also where its box extent is 1
+    for (int d = 0; d < p.n; ++d) {
+        if (t[d] == 1 && d != sa && d != sb) continue;
+        put(s.dA, &s.nA, d);
+        if (d < in_run_a) s.nAr = s.nA;
+    }
+    for (int k = 0; k < p.n; ++k) {
+        const int d = p.perm[k];
+        if (t[d] == 1 && d != sa && d != sb) continue;
+        put(s.dB, &s.nB, d);
+        if (k < in_run_b) s.nBr = s.nB;
+    }
+    // grid: indices with more than one step, in B's order, so that B is written
+    // as nearly one line after the other as the boxes allow
+    uint64_t tiles = 1;
+    for (int k = 0; k < p.n; ++k) {
+        const int d = p.perm[k];
+        if (t[d] == p.dim[d].size) continue;
+        if (s.ng == kBoxSteps) return false;
+        const uint64_t cnt = uint64_t((p.dim[d].size + t[d] - 1) / t[d]);
+        tiles *= cnt;
+        if (tiles >= (uint64_t(1) << 23)) return false;   // workgroups of one launch
+        BoxStep& g = s.g[s.ng++];
+        g.dv.init(uint32_t(cnt));
+        g.sa = uint32_t(t[d] * p.dim[d].sa);
+        g.sb = uint32_t(t[d] * p.dim[d].sb);
+        g.split = (d == sa ? 1 : 0) | (d == sb ? 2 : 0) | (d == b.sc ? 4 : 0);
+    }
+    s.ntiles = uint32_t(tiles);
+    s.chunk = tiles >= 1024 ? 5 : 0;
+    s.sizeA = sa >= 0 ? int(p.dim[sa].size) : 1;
+    s.sizeB = sb >= 0 ? int(p.dim[sb].size) : 1;
+    s.sizeC = b.sc >= 0 ? int(p.dim[b.sc].size) : 1;
+    return s.nA <= kBoxDims && s.nB <= kBoxDims && place(p, b, box_lds(elem_bytes(p.dtype), out->units), &s);
+}
+
+}  // namespace
+
+bool plan_box(const Problem& p, bool beta0, BoxPlan* out) {
+    if (p.family != TTX_FAMILY_MOVED && p.family != TTX_FAMILY_PRESERVED) return false;
+    if (p.dim[0].sa != 1 || p.dim[p.perm[0]].sb != 1) return false;
+    // offsets inside a box are unsigned 32-bit byte offsets
+    if (p.extent_a >= (int64_t(1) << 32) || p.extent_b >= (int64_t(1) << 32)) return false;
+    Box best;
+    double least = 1e300;
+    each_box(p, [&](const Box& b) {
+        const double c = box_cost(p, beta0, b);
+        if (c < least) least = c, best = b;
+    });
+    return least < 1e300 && make_box(p, beta0, best, out);
+}
+
+}  // namespace ttx

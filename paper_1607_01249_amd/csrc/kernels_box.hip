@@ -1,0 +1,39 @@
+// Launch of the box-tile kernels.
+#include "box_kernel.h"
+#include "ttx_internal.h"
+
+namespace ttx {
+
+template <typename T, typename S>
+static hipError_t launch_box_as(const BoxPlan& bp, bool beta0, const void* A, const void* Bsrc, void* Bdst,
+                                const Scalar& alpha, const Scalar& beta, hipStream_t stream) {
+    BoxArgs<T, S> a;
+    static_cast<BoxShape&>(a) = bp.s;
+    a.A = static_cast<const S*>(A);
+    a.Bsrc = static_cast<const T*>(Bsrc);
+    a.Bdst = static_cast<T*>(Bdst);
+    a.alpha = scalar_as<T>(alpha);
+    a.beta = scalar_as<T>(beta);
+    const dim3 g(a.ntiles), b(kThreads);
+    const auto kernel = bp.units == 2 ? (beta0 ? k_box<T, S, true, 2> : k_box<T, S, false, 2>)
+                                      : (beta0 ? k_box<T, S, true, 4> : k_box<T, S, false, 4>);
+    hipLaunchKernelGGL(kernel, g, b, 0, stream, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_box(const Problem& p, const BoxPlan& bp, bool beta0, const void* A, const void* Bsrc, void* Bdst,
+                      const Scalar& alpha, const Scalar& beta, hipStream_t stream) {
+    switch (p.code) {
+        case TTX_F32: return launch_box_as<float, float>(bp, beta0, A, Bsrc, Bdst, alpha, beta, stream);
+        case TTX_F64: return launch_box_as<double, double>(bp, beta0, A, Bsrc, Bdst, alpha, beta, stream);
+        case TTX_C32: return launch_box_as<cf32, cf32>(bp, beta0, A, Bsrc, Bdst, alpha, beta, stream);
+        case TTX_C64: return launch_box_as<cf64, cf64>(bp, beta0, A, Bsrc, Bdst, alpha, beta, stream);
+        case TTX_F32_F64: return launch_box_as<double, float>(bp, beta0, A, Bsrc, Bdst, alpha, beta, stream);
+        case TTX_F64_F32: return launch_box_as<float, double>(bp, beta0, A, Bsrc, Bdst, alpha, beta, stream);
+        case TTX_C32_C64: return launch_box_as<cf64, cf32>(bp, beta0, A, Bsrc, Bdst, alpha, beta, stream);
+        case TTX_C64_C32: return launch_box_as<cf32, cf64>(bp, beta0, A, Bsrc, Bdst, alpha, beta, stream);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace ttx

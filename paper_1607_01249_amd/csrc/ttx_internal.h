@@ -250,6 +250,11 @@ const char* element_type_name(int dtype);
 std::string kernel_name(const Problem& p, const ttx_config& c, bool beta0, const void* A,
                         const void* Bsrc, const void* Bdst);
 
+// Box tiles (box_plan.cpp, kernels_box.hip).
+struct BoxPlan;
+hipError_t launch_box(const Problem& p, const BoxPlan& bp, bool beta0, const void* A, const void* Bsrc, void* Bdst,
+                      const Scalar& alpha, const Scalar& beta, hipStream_t stream);
+
 // Zero bytes [0, width) of `height` rows that start `pitch` bytes apart
 // (dispatch.hip; width and pitch multiples of 4, dst 4-byte aligned).
 hipError_t launch_fill_zero(void* dst, int64_t width, int64_t height, int64_t pitch, hipStream_t stream);
