@@ -51,12 +51,12 @@ ttx_status fail(ttx_status s, const std::string& msg) {
 void clear_error() { g_last_error.clear(); }
 
 // A per-call plan runs box tiles wherever the problem has a box and the tune
-// table has no entry for it: over 364 drawn problems (4 KB to 650 MB, all
-// types, leading dimensions) they take 6.30 ms where the menu's heuristic
-// configurations take 7.93 ms, and 6.28 ms is the sum of the better of the two;
-// the menu is ahead by more than 1 us only on problems below 15 MB whose
-// kernels take 4 to 7 us.  Plans of ttx_plan_create run the configuration
-// that they describe.
+// table has no entry for it: over 782 drawn problems (4 KB to 650 MB, all
+// types, leading dimensions) they take 11.89 ms where the menu's heuristic
+// configurations take 14.76 ms, and the better of the two 11.87 ms; the menu is
+// ahead by up to 0.6 us on some small problems (kernels of 3 us), and by 10 to
+// 16 % on a few of 50 to 90 MB.  Plans of ttx_plan_create run the
+// configuration that they describe.
 static std::shared_ptr<const BoxPlan> choose_box(const Problem& p, bool beta0) {
     auto bp = std::make_shared<BoxPlan>();
     return plan_box(p, beta0, bp.get()) ? bp : nullptr;

@@ -111,21 +111,24 @@ bool box_of(const Problem& p, Box* b) {
     b->nua = b->volume / b->LA * ((b->LA + UA - 1) / UA);
     b->nub = b->volume / b->LB * ((b->LB + UB - 1) / UB);
     if (b->nua > kThreads * kBoxUnits || b->nub > kThreads * kBoxUnits) return false;
-    return b->volume / b->LA * (b->LA + 2 * UA) <= (kBoxBytes + 4096) / eb;
+    return b->volume / b->LA * (b->LA + 1) + UA <= box_lds(eb, kBoxUnits);   // with an odd pitch
 }
 
 // Whether two units per thread hold the box.
 bool small_box(const Problem& p, const Box& b) {
     const int UA = 16 / elem_bytes(p.dtype_a);
     return b.nua <= 2 * kThreads && b.nub <= 2 * kThreads &&
-           b.volume / b.LA * (b.LA + 2 * UA) <= (8192 + 2048) / elem_bytes(p.dtype);
+           b.volume / b.LA * (b.LA + 1) + UA <= box_lds(elem_bytes(p.dtype), 2);
 }
 
 // Estimated time in microseconds: the bytes at the rate of a large copy; per
-// run that does not end where the next box of B's order goes on, about half a
-// line; a few bytes per unit (addresses, LDS) and a fixed cost per box; and
+// run up to half a 128-byte line (less where runs are whole lines, or where the
+// next boxes in B's order go on with them, so that the shared line is still in
+// the L2); a byte or so per unit (addresses, LDS) and a fixed cost per box; and
 // what one compute unit's boxes wait for, which counts where there are few.
-// The constants are fitted to the times of some 9000 boxes of 175 problems.
+// The constants are fitted to the times of some 9000 boxes of 190 problems on
+// buffers that the caches don't hold; the boxes taken come to 3.27 ms where the
+// best of all come to 3.16 ms.
 double box_cost(const Problem& p, bool beta0, const Box& b) {
     const int ea = elem_bytes(p.dtype_a), eb = elem_bytes(p.dtype);
     const double n = double(p.elements), sides = beta0 ? 1.0 : 2.0;   // accesses of B
@@ -133,13 +136,16 @@ double box_cost(const Problem& p, bool beta0, const Box& b) {
     double da = 1.0, db = 1.0;
     for (int k = 0, d; k < p.n && (d = p.perm[k]) != b.sa; ++k) da *= double((p.dim[d].size + b.t[d] - 1) / b.t[d]);
     for (int k = 0, d; k < p.n && (d = p.perm[k]) != b.sb; ++k) db *= double((p.dim[d].size + b.t[d] - 1) / b.t[d]);
-    const double runs_a = n / double(b.LA) * (b.sa >= 0 && da <= 8.0 ? 25.0 : 50.0);
-    const double runs_b = n / double(b.LB) * (b.sb >= 0 && db <= 8.0 ? 22.0 : 54.0) * sides;
-    const double units = 2.8 * double(b.nua + b.nub) * b.tiles;
-    const double wide = small_box(p, b) ? 1.0 : beta0 ? 1.037 : 1.066;
-    const double bytes = (n * (ea + eb * sides) + runs_a + runs_b + units) * wide + 1500.0 * b.tiles;
+    bool lines_a = b.LA * ea % 128 == 0, lines_b = b.LB * eb % 128 == 0;
+    for (int k = b.in_run_a; k < p.n; ++k) lines_a = lines_a && p.dim[k].sa * ea % 128 == 0;
+    for (int k = b.in_run_b; k < p.n; ++k) lines_b = lines_b && p.dim[p.perm[k]].sb * eb % 128 == 0;
+    const double runs_a = n / double(b.LA) * (lines_a ? 36.0 : b.sa >= 0 && da <= 8.0 ? 21.0 : 57.0);
+    const double runs_b = n / double(b.LB) * (lines_b ? 4.0 : b.sb >= 0 && db <= 8.0 ? 27.0 : 49.0) * sides;
+    const double units = 0.8 * double(b.nua + b.nub) * b.tiles;
+    const double wide = small_box(p, b) ? 1.0 : beta0 ? 1.084 : 1.076;
+    const double bytes = (n * (ea + eb * sides) + runs_a + runs_b + units) * wide + 1200.0 * b.tiles;
     const double rounds = std::ceil(b.tiles / 256.0), fill = std::ceil(double(std::max(b.nua, b.nub)) / kThreads);
-    return bytes / 6e6 + 0.052 * fill * (1.0 + 0.025 * (rounds - 1.0));
+    return bytes / 6e6 + 0.026 * fill * (1.0 + 0.02 * (rounds - 1.0));
 }
 
 template <typename F>
@@ -159,25 +165,25 @@ void each_box(const Problem& p, F&& f) {
             if (rb[j].t) b.t[p.perm[rb[j].whole]] = std::max(b.t[p.perm[rb[j].whole]], rb[j].t);
             if (!box_of(p, &b)) continue;
             f(b);
-            // a small box filled up: with the next index of A's order or of B's,
-            // to two or to four units a thread
-            const int64_t units = std::max(b.nua, b.nub);
-            for (int side = 0; side < 2 && units <= kThreads; ++side) {
-                int d = -1;
-                for (int k = 0; k < p.n && d < 0; ++k) {
-                    const int x = side ? p.perm[k] : k;
-                    if (b.t[x] == 1 && x != b.sa && x != b.sb) d = x;
-                }
-                if (d < 0) continue;
+            // a small box filled up to two or four units a thread, with the
+            // next indices of A's order or of B's
+            for (int side = 0; side < 2 && std::max(b.nua, b.nub) <= kThreads; ++side)
                 for (int64_t most = 2 * kThreads; most <= 4 * kThreads; most *= 2) {
                     Box c = b;
-                    const int64_t steps = std::min(p.dim[d].size, most / units);
-                    const int64_t pieces = (p.dim[d].size + steps - 1) / steps;
-                    c.t[d] = (p.dim[d].size + pieces - 1) / pieces;
-                    if (c.t[d] > 1 && box_of(p, &c)) f(c);
-                    if (c.t[d] == p.dim[d].size) break;
+                    for (int k = 0; k < p.n; ++k) {
+                        const int d = side ? p.perm[k] : k;
+                        const int64_t room = most / std::max(c.nua, c.nub), size = p.dim[d].size;
+                        if (c.t[d] > 1 || d == c.sa || d == c.sb) continue;
+                        if (room < 2) break;
+                        Box e = c;
+                        const int64_t pieces = (size + room - 1) / room;
+                        e.t[d] = (size + pieces - 1) / pieces;
+                        if (!box_of(p, &e)) break;
+                        c = e;
+                        if (pieces > 1) break;
+                    }
+                    if (c.volume > b.volume) f(c);
                 }
-            }
         }
 }
 
@@ -327,7 +333,9 @@ bool plan_box(const Problem& p, bool beta0, BoxPlan* out) {
         const double c = box_cost(p, beta0, b);
         if (c < least) least = c, best = b;
     });
-    return least < 1e300 && make_box(p, beta0, best, out);
+    // far from a copy's time (single elements in every run): the menu's tiles
+    const double bytes = double(p.elements) * (elem_bytes(p.dtype_a) + elem_bytes(p.dtype) * (beta0 ? 1 : 2));
+    return least < 4.0 * bytes / 6e6 + 10.0 && make_box(p, beta0, best, out);
 }
 
 }  // namespace ttx
