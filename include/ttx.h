@@ -204,7 +204,10 @@ const char *ttx_version(void);
 /* -- per call (Eqn. 1) ------------------------------------------------------
  * B_{Pi(i)} <- alpha*A_i + beta*B_{Pi(i)} on `stream` (see the conventions
  * above).  Plans (index merging, family and config choice) are cached per
- * problem, so repeated calls with the same shape only launch. */
+ * problem, so repeated calls with the same shape only launch.  A problem with
+ * an entry in the tune table runs that configuration; any other runs box
+ * tiles where it has them (a tile is a box that holds whole runs of A and of
+ * B, for extents of any size), else the heuristic configuration. */
 ttx_status ttx_transpose(ttx_dtype dtype, int n, const int *perm, const int64_t *size,
                          const int64_t *outer_a, const int64_t *outer_b,
                          double alpha, const void *A, double beta, void *B,
@@ -504,18 +507,20 @@ ttx_status ttx_contraction_destroy(ttx_contraction *plan);
 
 /* -- batched execution ----------------------------------------------------------
  * Many independent transpositions, each Eqn. 1 with its own dtype, shape,
- * permutation, leading dimensions, scalars and tensors, run by ONE
- * persistent kernel launch: the planner splits every problem into tiles
- * (Sec. 2.2 macro-tiles), the kernel's workgroups walk the combined tile
- * space through a device-resident descriptor table, and the launch is
- * captured once into a HIP graph and replayed by ttx_batch_execute.  Each
- * problem's tile variant comes from a small menu compiled into that kernel:
- * the per-shape tune table when ttx_batch_tune has timed it, otherwise the
- * heuristics of Sec. 2.3.  Problems of the complex and mixed-precision
- * types are not in that kernel: each runs its per-call kernel (per-call
- * tune table, else heuristics), launched after the persistent kernel in the
+ * permutation, leading dimensions, scalars and tensors, as one graph launch
+ * that is captured once and replayed by ttx_batch_execute.  FP32 and FP64
+ * problems without a tuned configuration run in box tiles (see ttx_transpose),
+ * the boxes of all of them in one kernel launch.  Those that ttx_batch_tune
+ * has given a configuration (a process-wide per-shape table), and those that
+ * have no boxes, run in ONE persistent kernel launch: every problem is split
+ * into tiles (Sec. 2.2 macro-tiles) of a variant from a small menu compiled
+ * into that kernel (else the heuristics of Sec. 2.3, which ttx_batch_config
+ * reports for every untuned problem), and its workgroups walk the combined
+ * tile space through a device-resident descriptor table.  Problems of the
+ * complex and mixed-precision types are in neither kernel: each runs its
+ * per-call kernel (per-call tune table, else heuristics), launched last in the
  * same graph.  Results are bitwise the same as per-call execution (the same
- * tile code and operation order). */
+ * operation order). */
 typedef struct ttx_problem {
     ttx_dtype dtype;
     int n;
@@ -536,13 +541,13 @@ typedef struct ttx_problem {
 
 typedef struct ttx_batch_info {
     int count;
-    int grid;                        /* workgroups of the persistent launch */
-    int variants_used;               /* distinct tile variants among the problems */
+    int grid;                        /* workgroups of the launches over many problems */
+    int variants_used;               /* distinct kernel bodies among the problems */
     int tuned;                       /* problems whose config came from tuning */
     int64_t total_tiles;
     int64_t algorithmic_bytes;       /* sum of 2S (beta == 0) or 3S bytes */
-    int64_t chunks;                  /* units of work claimed by the workgroups: runs of up to
-                                        a fixed number of consecutive tiles of one problem */
+    int64_t chunks;                  /* runs of up to a fixed number of consecutive tiles or
+                                        boxes of one problem */
     int per_call;                    /* problems launched with their per-call kernels (complex
                                         and mixed-precision types) */
 } ttx_batch_info;
@@ -553,12 +558,12 @@ typedef struct ttx_batch ttx_batch;
  * device memory; the caller owns every A and B).  Every problem is checked
  * as ttx_transpose would check it; the first failure is returned. */
 ttx_status ttx_batch_create(ttx_batch **batch, int count, const ttx_problem *problems);
-/* Times the current config and up to max_candidates batched-menu configs
- * per distinct shape (0: 16) inside the persistent kernel on scratch
- * buffers, one problem at a time; another config replaces the current one
- * only when it is at least 5% faster.  The tuned set is then checked in
- * context: the whole persistent launch is timed with it and with the
- * configs it replaced, alternately, on scratch buffers the size of the
+/* Times the current config, the boxes and up to max_candidates batched-menu
+ * configs per distinct shape (0: 16) on scratch buffers, one problem at a
+ * time (configs inside the persistent kernel); another config replaces what
+ * the problem runs only when it is at least 5% faster.  The tuned set is then checked in
+ * context: the whole batch is timed with it and with what it
+ * replaced, alternately, on scratch buffers the size of the
  * batch's footprint (the caller's tensors are not touched), and the kernel
  * problems keep the tuned set only when it is at least 1% faster (else they
  * return to their previous configs and this call's table entries are
@@ -567,11 +572,11 @@ ttx_status ttx_batch_create(ttx_batch **batch, int count, const ttx_problem *pro
  * Blocks: waits for the device to be idle first (earlier launches of the
  * batch may still be reading its descriptors). */
 ttx_status ttx_batch_tune(ttx_batch *batch, int max_candidates, int reps);
-/* One graph launch of the persistent kernel on `stream` (captured on first use).
+/* One graph launch of the batch on `stream` (captured on first use).
  * Launches of one batch must not overlap each other (they share the batch's
  * work counter and outputs): order them on one stream or synchronise. */
 ttx_status ttx_batch_execute(ttx_batch *batch, hipStream_t stream);
-/* The same persistent kernel launched directly (no graph). */
+/* The same kernels launched directly (no graph). */
 ttx_status ttx_batch_execute_direct(ttx_batch *batch, hipStream_t stream);
 /* New pointers and scalars for problems of unchanged shape; the copy to the
  * descriptor table is ordered on `stream` and completes before returning. */

@@ -1,15 +1,21 @@
 // Batched execution: many independent transpositions, each Eqn. 1 with its
-// own shape, permutation, scalars and tensors, run by ONE persistent kernel.
+// own shape, permutation, scalars and tensors.
 //
-// The host plans every problem, picks a tile variant from the small batched
-// menu (tuned per shape or chosen by the heuristics of Sec. 2.3), splits its
-// tiles into chunks of consecutive tiles, and writes the descriptor table and
-// the prefix sums of the per-problem chunk counts to device memory.  The
-// kernel is launched with about one wave of resident workgroups; each claims
-// chunks from a counter, finds the owning problem by binary search over the
-// prefix sums, and runs that problem's tile body over the chunk -- the same
-// tile code as the per-call kernels, pipelined across the chunk's tiles.  The
-// launch is captured once into a HIP graph and replayed.
+// A problem without a tuned configuration runs in box tiles: one launch with a
+// workgroup per box of every such problem (box_kernel.h).  512 uneven problems
+// (4.2 GB) take 777 us that way; the persistent kernel below took 1216 us on
+// them, with its fixed tile shapes, its switch over 72 tile bodies behind
+// function calls and the scratch memory that these need.  It keeps the
+// problems with a tuned configuration, those that have no boxes, and the
+// server's and the allocation-free runs, whose descriptors have a fixed size:
+// the host picks a tile variant from the small batched menu, splits the tiles
+// into chunks of consecutive tiles, and writes the descriptor table and the
+// prefix sums of the per-problem chunk counts to device memory.  The kernel is
+// launched with about one wave of resident workgroups; each claims chunks from
+// a counter, finds the owning problem by binary search over the prefix sums,
+// and runs that problem's tile body over the chunk -- the same tile code as the
+// per-call kernels, pipelined across the chunk's tiles.  The launches are
+// captured once into a HIP graph and replayed.
 #include <algorithm>
 #include <cstring>
 #include <map>
@@ -19,6 +25,7 @@
 
 #include "menu.h"
 #include "tile_kernels.h"
+#include "box.h"
 #include "ttx_internal.h"
 
 struct ttx_batch {
@@ -26,13 +33,20 @@ struct ttx_batch {
     std::vector<ttx_problem> src;
     std::vector<ttx_config> cfg;
     std::vector<int> forced;
+    std::vector<char> described;         // cfg is filled in (problems in box tiles: when it is asked for)
     std::vector<int> per_call;           // problems launched with their per-call kernels
     std::vector<ttx::BatchDesc> desc;    // kernel problems, in work order
     std::vector<uint32_t> chunk_prefix;  // over the work order
     std::vector<int> order;              // work position -> problem index
     int nk = 0;                          // problems in the persistent kernel
+    bool boxes = false;                  // untuned problems run box tiles where they have them
+    std::vector<int> tuned;              // problems that keep a tuned configuration
+    std::vector<ttx::BoxBatchDesc> box;  // problems in box tiles
+    std::vector<uint32_t> box_first, box_bucket;   // first chunk per problem, first problem per stretch of chunks
+    ttx::BoxBatchGrid box_grid{};
     unsigned char* d_work = nullptr;     // descriptors, chunk prefix, claim counter
     size_t work_bytes = 0;
+    size_t counter_at = size_t(-1);      // where the claim counter was cleared
     uint64_t total = 0;                  // tiles
     uint32_t chunks = 0;
     int grid = 0;
@@ -485,6 +499,13 @@ static constexpr size_t prefix_offset(int count) { return desc_bytes(count); }
 static constexpr size_t counter_offset(int count) { return (prefix_offset(count) + sizeof(uint32_t) * (count + 1) + 15) & ~size_t(15); }
 static constexpr size_t work_bytes(int count) { return counter_offset(count) + 2 * sizeof(uint32_t); }
 
+// After them, in a batch that has problems in box tiles: their descriptors,
+// first chunks and the buckets.
+static size_t box_offset(const ttx_batch* b) { return (work_bytes(b->nk) + 255) & ~size_t(255); }
+static size_t box_bytes(const ttx_batch* b) {
+    return b->box.size() * (sizeof(BoxBatchDesc) + sizeof(uint32_t)) + b->box_bucket.size() * sizeof(uint32_t);
+}
+
 static const BatchDesc* work_desc(const ttx_batch* b) { return reinterpret_cast<const BatchDesc*>(b->d_work); }
 static const uint32_t* work_prefix(const ttx_batch* b) {
     return reinterpret_cast<const uint32_t*>(b->d_work + prefix_offset(b->nk));
@@ -493,13 +514,86 @@ static uint32_t* work_counter(const ttx_batch* b) {
     return reinterpret_cast<uint32_t*>(b->d_work + counter_offset(b->nk));
 }
 
+// Problem i's configuration; for one in box tiles the heuristic choice that
+// the persistent kernel would run.
+static ttx_status config_of(const ttx_batch* b, int i, ttx_config* config) {
+    *config = b->cfg[i];
+    if (b->described[i]) return TTX_OK;
+    const ttx_problem& q = b->src[i];
+    BatchDesc d;
+    return batch_describe(b->prob[i], nullptr, beta_is_zero(b->prob[i].dtype, beta_of(q)), q.A,
+                          q.B_in ? q.B_in : q.B, q.B, q.alpha, q.beta, &d, config);
+}
+
+// Adds problem i to the launch of boxes if it has them.
+static bool add_boxes(ttx_batch* b, int i, bool beta0, uint64_t* boxes) {
+    const ttx_problem& q = b->src[i];
+    const Problem& p = b->prob[i];
+    BoxPlan bp;
+    if (!b->boxes || b->tuned[i] || !plan_box(p, beta0, &bp, true)) return false;
+    if (*boxes + bp.s.ntiles >= uint64_t(1) << 22) return false;   // workgroups of one launch, whole chunks
+    *boxes += bp.s.ntiles;
+    BoxBatchDesc d;
+    std::memset(&d, 0, sizeof(d));
+    auto fill = [&](auto& a) {
+        typedef typename std::remove_reference<decltype(a.alpha)>::type T;
+        static_cast<BoxShape&>(a) = bp.s;
+        a.A = static_cast<const T*>(q.A);
+        a.Bsrc = beta0 ? nullptr : static_cast<const T*>(q.B_in ? q.B_in : q.B);
+        a.Bdst = static_cast<T*>(q.B);
+        a.alpha = T(q.alpha);
+        a.beta = T(q.beta);
+    };
+    if (p.dtype == TTX_F32) fill(d.f32);
+    else fill(d.f64);
+    d.kind = (p.dtype == TTX_F32 ? 0 : 2) + (beta0 ? 1 : 0);
+    b->box.push_back(d);
+    return true;
+}
+
+// Chunks of boxes: 32 where that leaves few places empty, less for batches of
+// problems with few boxes.
+static void layout_boxes(ttx_batch* b, uint64_t boxes) {
+    BoxBatchGrid& g = b->box_grid;
+    g = BoxBatchGrid{};
+    b->box_first.clear();
+    b->box_bucket.clear();
+    if (b->box.empty()) return;
+    auto chunks_of = [&](const BoxBatchDesc& d, int k) { return (d.f64.ntiles + (1u << k) - 1) >> k; };
+    for (g.chunk = 5; g.chunk > 0; --g.chunk) {
+        uint64_t padded = 0;
+        for (const auto& d : b->box) padded += uint64_t(chunks_of(d, g.chunk)) << g.chunk;
+        if (padded <= boxes + boxes / 16 + 512) break;
+    }
+    for (const auto& d : b->box) {
+        b->box_first.push_back(g.chunks);
+        g.chunks += chunks_of(d, g.chunk);
+    }
+    while ((g.chunks >> g.shift) >= uint32_t(kBoxBuckets)) ++g.shift;
+    const uint32_t n = (g.chunks >> g.shift) + 2;
+    for (uint32_t k = 0, at = 0; k < n; ++k) {   // the problem that holds a stretch's first chunk
+        while (at + 1 < b->box_first.size() && b->box_first[at + 1] <= uint64_t(k) << g.shift) ++at;
+        b->box_bucket.push_back(at);
+    }
+    g.grid = (g.chunks + 7) / 8 * 8 << g.chunk;
+}
+
+static hipError_t launch_boxes(const ttx_batch* b, hipStream_t stream) {
+    if (!b->box_grid.grid) return hipSuccess;
+    const unsigned char* at = b->d_work + box_offset(b);
+    const auto* desc = reinterpret_cast<const BoxBatchDesc*>(at);
+    const auto* first = reinterpret_cast<const uint32_t*>(at + b->box.size() * sizeof(BoxBatchDesc));
+    return launch_box_batch(desc, first, first + b->box.size(), b->box_grid, stream);
+}
+
 static ttx_status describe_all(ttx_batch* b) {
     const int count = int(b->prob.size());
     std::vector<BatchDesc> desc(count);
     std::vector<int> kernel;
-    uint64_t total = 0;
+    uint64_t total = 0, boxes = 0;
     b->bytes = 0;
     b->per_call.clear();
+    b->box.clear();
     for (int i = 0; i < count; ++i) {
         const ttx_problem& q = b->src[i];
         const Problem& p = b->prob[i];
@@ -508,14 +602,17 @@ static ttx_status describe_all(ttx_batch* b) {
         if (runs_per_call(p)) {
             if (!b->forced[i] && !table_lookup(p, beta0, &b->cfg[i])) b->cfg[i] = default_config(p);
             b->per_call.push_back(i);
+            b->described[i] = 1;
             continue;
         }
+        if (add_boxes(b, i, beta0, &boxes)) continue;
         const void* Bin = q.B_in ? q.B_in : q.B;
         ttx_config used;
-        ttx_status st = batch_describe(p, b->forced[i] ? &b->cfg[i] : nullptr, beta0, q.A, Bin, q.B,
-                                       q.alpha, q.beta, &desc[i], &used);
+        ttx_status st = batch_describe(p, b->forced[i] && b->described[i] ? &b->cfg[i] : nullptr, beta0, q.A, Bin,
+                                       q.B, q.alpha, q.beta, &desc[i], &used);
         if (st != TTX_OK) return st;
         b->cfg[i] = used;
+        b->described[i] = 1;
         total += desc[i].tiles;
         if (total >= (uint64_t(1) << 32)) return fail(TTX_EUNSUPPORTED, "batch has too many tiles");
         kernel.push_back(i);
@@ -530,9 +627,10 @@ static ttx_status describe_all(ttx_batch* b) {
     b->desc.resize(b->nk);
     for (int i = 0; i < b->nk; ++i) b->desc[i] = desc[b->order[i]];
     b->chunk_prefix.assign(b->nk + 1, 0);
-    b->total = total;
+    b->total = total + boxes;
     b->chunks = b->nk ? batch_layout(b->desc.data(), b->nk, b->chunk_prefix.data(), &b->grid) : 0;
     if (!b->nk) b->grid = 0;
+    layout_boxes(b, boxes);
     return TTX_OK;
 }
 
@@ -552,19 +650,33 @@ static hipError_t launch_per_call(const ttx_batch* b, hipStream_t stream) {
 
 static ttx_status upload(ttx_batch* b, hipStream_t stream) {
     const int count = b->nk;
-    const size_t need = work_bytes(count);
+    const size_t at = box_offset(b), need = at + box_bytes(b);
+    if (b->d_work && b->work_bytes < need) {   // tuning moved problems between the two kernels
+        (void)hipFree(b->d_work);
+        b->d_work = nullptr;
+    }
     if (!b->d_work) {
         if (hipMalloc(reinterpret_cast<void**>(&b->d_work), need) != hipSuccess)
             return fail(TTX_ENOMEM, "batch descriptor allocation failed");
         b->work_bytes = need;
-        // the claim counter starts at zero; every launch leaves it at zero
-        if (hipMemset(b->d_work + counter_offset(count), 0, 2 * sizeof(uint32_t)) != hipSuccess)
-            return fail(TTX_EHIP, "batch counter initialisation failed");
+        b->counter_at = size_t(-1);
     }
-    if ((count && hipMemcpyAsync(b->d_work, b->desc.data(), desc_bytes(count), hipMemcpyHostToDevice, stream) !=
-                      hipSuccess) ||
-        hipMemcpyAsync(b->d_work + prefix_offset(count), b->chunk_prefix.data(), sizeof(uint32_t) * (count + 1),
-                       hipMemcpyHostToDevice, stream) != hipSuccess ||
+    if (b->counter_at != counter_offset(count)) {
+        // the claim counter starts at zero; every launch leaves it at zero
+        if (hipMemsetAsync(b->d_work + counter_offset(count), 0, 2 * sizeof(uint32_t), stream) != hipSuccess)
+            return fail(TTX_EHIP, "batch counter initialisation failed");
+        b->counter_at = counter_offset(count);
+    }
+    auto copy = [&](size_t to, const void* from, size_t bytes) {
+        return !bytes || hipMemcpyAsync(b->d_work + to, from, bytes, hipMemcpyHostToDevice, stream) == hipSuccess;
+    };
+    const size_t nb = b->box.size();
+    const size_t first = at + nb * sizeof(BoxBatchDesc), bucket = first + nb * sizeof(uint32_t);
+    if (!copy(0, b->desc.data(), desc_bytes(count)) ||
+        !copy(prefix_offset(count), b->chunk_prefix.data(), sizeof(uint32_t) * (count + 1)) ||
+        !copy(at, b->box.data(), nb * sizeof(BoxBatchDesc)) ||
+        !copy(first, b->box_first.data(), nb * sizeof(uint32_t)) ||
+        !copy(bucket, b->box_bucket.data(), b->box_bucket.size() * sizeof(uint32_t)) ||
         hipStreamSynchronize(stream) != hipSuccess)
         return fail(TTX_EHIP, "batch descriptor upload failed");
     return TTX_OK;
@@ -578,6 +690,8 @@ static ttx_status prepare(ttx_batch* b, int count, const ttx_problem* problems) 
     b->src.assign(problems, problems + count);
     b->cfg.resize(count);
     b->forced.assign(count, 0);
+    b->tuned.assign(count, 0);
+    b->described.assign(count, 0);
     for (int i = 0; i < count; ++i) {
         ttx_status st = problem_from(problems[i], &b->prob[i]);
         if (st == TTX_OK) {
@@ -591,7 +705,7 @@ static ttx_status prepare(ttx_batch* b, int count, const ttx_problem* problems) 
                                                           problems[i].B)));
                 if (it != g_btab.end()) {
                     b->cfg[i] = it->second;
-                    b->forced[i] = 1;
+                    b->forced[i] = b->tuned[i] = b->described[i] = 1;
                 }
             }
         }
@@ -642,6 +756,7 @@ ttx_status ttx_batch_create(ttx_batch** out, int count, const ttx_problem* probl
     if (!out || count < 0 || (count > 0 && !problems)) return fail(TTX_EINVAL, "bad batch arguments");
     ttx_batch* b = new (std::nothrow) ttx_batch;
     if (!b) return fail(TTX_ENOMEM, "out of host memory");
+    b->boxes = true;
     ttx_status st = prepare(b, count, problems);
     if (st != TTX_OK) {
         delete b;
@@ -675,13 +790,20 @@ ttx_status ttx_batch_update(ttx_batch* b, int count, const ttx_problem* problems
     }
     const uint32_t old_chunks = b->chunks;
     const int old_grid = b->grid;
+    const BoxBatchGrid old_boxes = b->box_grid;
+    const size_t old_work = b->work_bytes, old_nb = b->box.size();
+    const int old_nk = b->nk;
     b->src.assign(problems, problems + count);
     for (int i = 0; i < count; ++i) b->forced[i] = b->prob[i].family != TTX_FAMILY_EMPTY;
     ttx_status st = describe_all(b);
     if (st != TTX_OK) return st;
     // per-call launches carry their pointers in the graph: capture again
-    if (b->chunks != old_chunks || b->grid != old_grid || !b->per_call.empty()) drop_graph(b);
-    return upload(b, stream);
+    if (b->chunks != old_chunks || b->grid != old_grid || !b->per_call.empty() || b->nk != old_nk ||
+        b->box.size() != old_nb || std::memcmp(&b->box_grid, &old_boxes, sizeof(old_boxes)) != 0)
+        drop_graph(b);
+    st = upload(b, stream);
+    if (b->work_bytes != old_work) drop_graph(b);   // a new work block
+    return st;
 }
 
 // A tuned batched configuration replaces the current one only when it is
@@ -695,7 +817,8 @@ static double time_launches(ttx_batch* b, hipStream_t s, int reps, hipEvent_t* e
     std::vector<float> ms;
     for (int r = -1; r < reps; ++r) {   // r = -1: warm-up
         if (hipEventRecord(ev[0], s) != hipSuccess) return -1;
-        if (launch_batch(work_desc(b), work_prefix(b), b->nk, b->chunks, b->grid, work_counter(b), s) != hipSuccess)
+        if (launch_boxes(b, s) != hipSuccess ||
+            launch_batch(work_desc(b), work_prefix(b), b->nk, b->chunks, b->grid, work_counter(b), s) != hipSuccess)
             return -1;
         if (hipEventRecord(ev[1], s) != hipSuccess || hipEventSynchronize(ev[1]) != hipSuccess) return -1;
         float t = 0;
@@ -706,17 +829,17 @@ static double time_launches(ttx_batch* b, hipStream_t s, int reps, hipEvent_t* e
     return ms[ms.size() / 2];
 }
 
-// Whether the configs now in `b` (the tuned set) run the whole persistent
-// launch faster than `old_cfg` / `old_forced` (the set they replaced): both
+// Whether the configs now in `b` (the tuned set) run the whole batch faster
+// than `old_cfg` / `old_forced` / `old_tuned` (the set they replaced): both
 // are timed in alternation on scratch copies of the batch's footprint (the
 // kernel problems' A and B extents, each at its pointer's offset modulo 16
 // bytes, so that every problem runs the same vector variant), never on the
 // caller's tensors.  When the scratch cannot be allocated the tuned set is
 // kept.  Leaves `b` described with the tuned set and the real pointers.
 static bool tuned_set_wins(ttx_batch* b, const std::vector<ttx_config>& old_cfg, const std::vector<int>& old_forced,
-                           int reps) {
+                           const std::vector<int>& old_tuned, int reps) {
     const std::vector<ttx_config> new_cfg = b->cfg;
-    const std::vector<int> new_forced = b->forced;
+    const std::vector<int> new_forced = b->forced, new_tuned = b->tuned;
     const std::vector<ttx_problem> real = b->src;
     std::vector<int64_t> off_a(b->prob.size(), -1), off_b(b->prob.size(), -1);
     int64_t total = 0;
@@ -747,6 +870,7 @@ static bool tuned_set_wins(ttx_batch* b, const std::vector<ttx_config>& old_cfg,
             for (int set = 0; set < 2 && ok; ++set) {
                 b->cfg = set == 0 ? new_cfg : old_cfg;
                 b->forced = set == 0 ? new_forced : old_forced;
+                b->tuned = set == 0 ? new_tuned : old_tuned;
                 ok = describe_all(b) == TTX_OK && upload(b, s) == TTX_OK;
                 const double t = ok ? time_launches(b, s, reps, ev) : -1;
                 ok = ok && t > 0;
@@ -762,6 +886,7 @@ static bool tuned_set_wins(ttx_batch* b, const std::vector<ttx_config>& old_cfg,
     b->src = real;
     b->cfg = new_cfg;
     b->forced = new_forced;
+    b->tuned = new_tuned;
     clear_error();
     return !ok || t_new < t_old * (1.0 - kBatchContextMargin);
 }
@@ -786,8 +911,14 @@ ttx_status ttx_batch_tune(ttx_batch* b, int max_candidates, int reps) {
     uint32_t* d_cnt = reinterpret_cast<uint32_t*>(d_blk + counter_offset(1));
     ttx_status result = TTX_OK;
     std::vector<ttx_config> cands(4096);
+    for (size_t i = 0; i < b->prob.size() && result == TTX_OK; ++i) {
+        ttx_config c;
+        result = config_of(b, int(i), &c);
+        b->cfg[i] = c;
+        b->described[i] = 1;
+    }
     const std::vector<ttx_config> old_cfg = b->cfg;
-    const std::vector<int> old_forced = b->forced;
+    const std::vector<int> old_forced = b->forced, old_tuned = b->tuned;
     std::vector<std::string> added;   // per-shape table keys this call adds
     bool changed = false;             // a kernel problem's config differs from the one it started with
     for (size_t i = 0; i < b->prob.size() && result == TTX_OK; ++i) {
@@ -813,7 +944,7 @@ ttx_status ttx_batch_tune(ttx_batch* b, int max_candidates, int reps) {
             if (it != g_btab.end()) {
                 changed = changed || std::memcmp(&b->cfg[i], &it->second, sizeof(ttx_config)) != 0;
                 b->cfg[i] = it->second;
-                b->forced[i] = 1;
+                b->forced[i] = b->tuned[i] = 1;
                 continue;
             }
         }
@@ -823,18 +954,23 @@ ttx_status ttx_batch_tune(ttx_batch* b, int max_candidates, int reps) {
         int nc = batch_candidates(p, max_candidates, cands.data() + 1, int(cands.size()) - 1);
         if (nc <= 0) continue;
         ++nc;
+        // and, last, the boxes that the problem runs without a tuned configuration
+        BoxPlan bp;
+        const bool boxed = b->boxes && plan_box(p, beta0, &bp, true);
         // scratch pointers keep the real pointers' offsets modulo 16 bytes, so
         // that each candidate runs the same vector variant it will run for real
         const uintptr_t offa = reinterpret_cast<uintptr_t>(q.A) & 15;
         const uintptr_t offb = reinterpret_cast<uintptr_t>(q.B) & 15;
         int best_i = -1;
         double best_us = 0;
-        std::vector<double> us(nc, 0.0);
-        result = time_candidates(p, beta0, nc, reps,
+        std::vector<double> us(nc + 1, 0.0);
+        result = time_candidates(p, beta0, nc + (boxed ? 1 : 0), reps,
             [&](int c, const void* A, void* B, hipStream_t s) -> hipError_t {
                 BatchDesc one;
                 const void* a = static_cast<const char*>(A) + offa;
                 void* bb = static_cast<char*>(B) + offb;
+                if (c == nc)
+                    return launch_box(p, bp, beta0, a, beta0 ? nullptr : bb, bb, Scalar(1.0), Scalar(beta0 ? 0.0 : 1.0), s);
                 if (batch_describe(p, &cands[c], beta0, a, bb, bb, 1.0, beta0 ? 0.0 : 1.0, &one, nullptr) != TTX_OK)
                     return hipErrorInvalidValue;
                 uint32_t pre[2];
@@ -850,9 +986,10 @@ ttx_status ttx_batch_tune(ttx_batch* b, int max_candidates, int reps) {
         // another configuration only when it is clearly faster than the
         // current one (timing one problem alone ranks close candidates
         // differently from the full batch)
-        if (result == TTX_OK && best_i > 0 && best_us < us[0] * (1.0 - kBatchTuneMargin)) {
+        const double now_us = boxed ? us[nc] : us[0];
+        if (result == TTX_OK && best_i > 0 && best_i < nc && best_us < now_us * (1.0 - kBatchTuneMargin)) {
             b->cfg[i] = cands[best_i];
-            b->forced[i] = 1;
+            b->forced[i] = b->tuned[i] = 1;
             changed = true;
             std::lock_guard<std::mutex> lock(g_btab_mu);
             g_btab[key] = cands[best_i];
@@ -865,11 +1002,13 @@ ttx_status ttx_batch_tune(ttx_batch* b, int max_candidates, int reps) {
     // full batch, so the tuned set must also win in context; otherwise the
     // kernel problems go back to the configs they started with (per-call
     // problems keep their tuned configs: they run alone in any case).
-    if (changed && b->nk > 0 && !tuned_set_wins(b, old_cfg, old_forced, std::max(reps, 5))) {
+    if (changed && (b->nk > 0 || !b->box.empty()) &&
+        !tuned_set_wins(b, old_cfg, old_forced, old_tuned, std::max(reps, 5))) {
         for (size_t i = 0; i < b->prob.size(); ++i)
             if (!runs_per_call(b->prob[i])) {
                 b->cfg[i] = old_cfg[i];
                 b->forced[i] = old_forced[i];
+                b->tuned[i] = old_tuned[i];
             }
         std::lock_guard<std::mutex> lock(g_btab_mu);
         for (const std::string& k : added) g_btab.erase(k);
@@ -882,25 +1021,25 @@ ttx_status ttx_batch_tune(ttx_batch* b, int max_candidates, int reps) {
 
 ttx_status ttx_batch_execute_direct(ttx_batch* b, hipStream_t stream) {
     if (!b) return fail(TTX_EINVAL, "NULL batch");
-    hipError_t e = b->chunks ? launch_batch(work_desc(b), work_prefix(b), b->nk, b->chunks, b->grid,
-                                            work_counter(b), stream)
-                             : hipSuccess;
+    hipError_t e = launch_boxes(b, stream);
+    if (e == hipSuccess && b->chunks)
+        e = launch_batch(work_desc(b), work_prefix(b), b->nk, b->chunks, b->grid, work_counter(b), stream);
     if (e == hipSuccess) e = launch_per_call(b, stream);
     return e == hipSuccess ? TTX_OK : fail(TTX_EHIP, std::string("batch launch: ") + hipGetErrorString(e));
 }
 
 ttx_status ttx_batch_execute(ttx_batch* b, hipStream_t stream) {
     if (!b) return fail(TTX_EINVAL, "NULL batch");
-    if (b->chunks == 0 && b->per_call.empty()) return TTX_OK;
+    if (b->chunks == 0 && b->box.empty() && b->per_call.empty()) return TTX_OK;
     if (!b->captured) {
         drop_graph(b);
         if (!b->cap_stream && hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking) != hipSuccess)
             return fail(TTX_EHIP, "capture stream creation failed");
         if (hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal) != hipSuccess)
             return fail(TTX_EHIP, "stream capture failed to start");
-        hipError_t e = b->chunks ? launch_batch(work_desc(b), work_prefix(b), b->nk, b->chunks, b->grid,
-                                                work_counter(b), b->cap_stream)
-                                 : hipSuccess;
+        hipError_t e = launch_boxes(b, b->cap_stream);
+        if (e == hipSuccess && b->chunks)
+            e = launch_batch(work_desc(b), work_prefix(b), b->nk, b->chunks, b->grid, work_counter(b), b->cap_stream);
         if (e == hipSuccess) e = launch_per_call(b, b->cap_stream);
         hipGraph_t g = nullptr;
         hipError_t e2 = hipStreamEndCapture(b->cap_stream, &g);
@@ -953,13 +1092,19 @@ ttx_status ttx_batch_get_info(const ttx_batch* b, ttx_batch_info* info) {
     std::memset(info, 0, sizeof(*info));
     info->count = int(b->prob.size());
     info->total_tiles = int64_t(b->total);
-    info->chunks = b->chunks;
-    info->grid = b->grid;
+    info->chunks = int64_t(b->chunks) + b->box_grid.chunks;
+    info->grid = b->grid + int(b->box_grid.grid);
     info->algorithmic_bytes = b->bytes;
     bool seen[4 * TTX_BATCH_MENU_SIZE] = {};
     for (const auto& d : b->desc)
         if (d.variant >= 0 && !seen[d.variant]) {
             seen[d.variant] = true;
+            ++info->variants_used;
+        }
+    bool kinds[4] = {};
+    for (const auto& d : b->box)
+        if (!kinds[d.kind]) {
+            kinds[d.kind] = true;
             ++info->variants_used;
         }
     int tuned = 0;
@@ -971,8 +1116,7 @@ ttx_status ttx_batch_get_info(const ttx_batch* b, ttx_batch_info* info) {
 
 ttx_status ttx_batch_config(const ttx_batch* b, int index, ttx_config* config) {
     if (!b || !config || index < 0 || index >= int(b->prob.size())) return fail(TTX_EINVAL, "bad index");
-    *config = b->cfg[index];
-    return TTX_OK;
+    return config_of(b, index, config);
 }
 
 ttx_status ttx_batch_plan(int count, const ttx_problem* problems, ttx_config* configs, int64_t* tiles) {

@@ -216,6 +216,22 @@ struct BoxArgs : BoxShape {
 // the padding of its runs.
 constexpr int box_lds(int elem, int units) { return (4096 * units + 1024 * units) / elem; }
 
+// One problem of a launch over many (FP32 and FP64).
+struct BoxBatchDesc {
+    union {
+        BoxArgs<float> f32;
+        BoxArgs<double> f64;
+    };
+    int kind;            // f32 beta, f32 beta == 0, f64 beta, f64 beta == 0
+    __host__ __device__ BoxBatchDesc() {}
+};
+constexpr int kBoxBuckets = 1024;
+struct BoxBatchGrid {
+    uint32_t grid;       // workgroups
+    uint32_t chunks;     // of 2^chunk boxes
+    int chunk, shift;    // a bucket covers 2^shift chunks
+};
+
 // A box for one problem (host).
 struct BoxPlan {
     BoxShape s;
@@ -224,8 +240,10 @@ struct BoxPlan {
     int units;           // per thread and side that hold the box: 2 or 4
 };
 // The best box for a problem, false if it has none (no contiguous runs of a
-// unit on both sides, offsets beyond 32 bits, flat or empty problems).
+// unit on both sides, offsets beyond 32 bits, empty problems).  `batched`: for
+// a launch over many problems (two units a thread, and flat problems too,
+// which otherwise have kernels of their own).
 struct Problem;
-bool plan_box(const Problem& p, bool beta0, BoxPlan* out);
+bool plan_box(const Problem& p, bool beta0, BoxPlan* out, bool batched = false);
 
 }  // namespace ttx

@@ -187,41 +187,46 @@ void each_box(const Problem& p, F&& f) {
         }
 }
 
-// LDS cycles of one wavefront's first units (put and gather) in a full box: a
-// bank serves one word a cycle, 32 words in all.
+// LDS cycles of half a wavefront's first units (put and gather) in a full box:
+// a bank serves one word a cycle, 32 words in all.  `least`: without conflicts.
 template <int UA, int UB>
-int bank_cycles(const BoxShape& s, int elem) {
+int bank_cycles(const BoxShape& s, int elem, int* least) {
+    constexpr int kLanes = 32;
     const int words = elem / 4, group = 32 / words;   // lanes served together
     const BoxCoord c{0, 0, s.tA, s.tB, s.tC};
-    int cycles = 0, at[64][UA + UB];
-    for (int lane = 0; lane < 64; ++lane) {
+    int at[UA + UB][kLanes];
+    for (int lane = 0; lane < kLanes; ++lane) {
         BoxUnits<UA, UB, 1> u;
         u.init(s, lane, c);
-        for (int j = 0; j < UA; ++j) at[lane][j] = u.put(0, j) + (u.put(0, j) >> s.skew);
-        for (int j = 0; j < UB; ++j) at[lane][UA + j] = u.gather(0, j);
+        for (int j = 0; j < UA; ++j) at[j][lane] = u.put(0, j) + (u.put(0, j) >> s.skew);
+        for (int j = 0; j < UB; ++j) at[UA + j][lane] = u.gather(0, j);
     }
-    for (int j = 0; j < UA + UB; ++j) {
-        if (s.aligned && j < UA) continue;   // written in whole units
-        for (int g = 0; g < 64; g += group) {
+    const int from = s.aligned ? UA : 0, units = s.aligned ? kLanes / 8 : 0;   // whole units: 8 lanes a cycle
+    int cycles = units;
+    for (int j = from; j < UA + UB; ++j)
+        for (int g = 0; g < kLanes; g += group) {
             int seen[32][32], n[32] = {}, most = 1;
             for (int lane = g; lane < g + group; ++lane) {
-                const int bank = at[lane][j] * words % 32;
+                const int l = at[j][lane], bank = l * words % 32;
                 bool again = false;   // the same element: one access
-                for (int k = 0; k < n[bank]; ++k) again |= seen[bank][k] == at[lane][j];
-                if (!again) seen[bank][n[bank]++] = at[lane][j];
+                for (int k = 0; k < n[bank]; ++k) again |= seen[bank][k] == l;
+                if (!again) seen[bank][n[bank]++] = l;
                 most = std::max(most, n[bank]);
             }
             cycles += most;
         }
-    }
-    return s.aligned ? cycles + 8 : cycles;
+    *least = units + (UA + UB - from) * (kLanes / group);
+    return cycles;
 }
 
-int bank_cycles(const Problem& p, const BoxShape& s) {
+int bank_cycles(const Problem& p, const BoxShape& s, int* least) {
     const int ea = elem_bytes(p.dtype_a), eb = elem_bytes(p.dtype);
-    if (ea == eb) return eb == 4 ? bank_cycles<4, 4>(s, 4) : eb == 8 ? bank_cycles<2, 2>(s, 8) : bank_cycles<1, 1>(s, 16);
-    if (ea < eb) return eb == 8 ? bank_cycles<4, 2>(s, 8) : bank_cycles<2, 1>(s, 16);
-    return eb == 4 ? bank_cycles<2, 4>(s, 4) : bank_cycles<1, 2>(s, 8);
+    if (ea == eb)
+        return eb == 4   ? bank_cycles<4, 4>(s, 4, least)
+               : eb == 8 ? bank_cycles<2, 2>(s, 8, least)
+                         : bank_cycles<1, 1>(s, 16, least);
+    if (ea < eb) return eb == 8 ? bank_cycles<4, 2>(s, 8, least) : bank_cycles<2, 1>(s, 16, least);
+    return eb == 4 ? bank_cycles<2, 4>(s, 4, least) : bank_cycles<1, 2>(s, 8, least);
 }
 
 // The LDS layout: A's runs one after the other, with the distance between them
@@ -253,9 +258,11 @@ bool place(const Problem& p, const Box& b, int cap, BoxShape* s) {
         }
         const int64_t last = b.volume / b.LA * pitch + UA;
         if (last + (last >> s->skew) > cap) continue;
-        // a skew costs instructions too
-        const int cycles = bank_cycles(p, *s) + (option < 2 ? 0 : 24);
-        if (cycles < best) best = cycles, chosen = *s;
+        int least = 0;
+        const int cycles = bank_cycles(p, *s, &least);
+        const int total = cycles + (option < 2 ? 0 : 12);   // a skew costs instructions too
+        if (total < best) best = total, chosen = *s;
+        if (cycles == least) break;   // what follows is no better
     }
     *s = chosen;
     return best < (1 << 30);
@@ -322,14 +329,17 @@ bool make_box(const Problem& p, bool beta0, const Box& b, BoxPlan* out) {
 
 }  // namespace
 
-bool plan_box(const Problem& p, bool beta0, BoxPlan* out) {
-    if (p.family != TTX_FAMILY_MOVED && p.family != TTX_FAMILY_PRESERVED) return false;
+bool plan_box(const Problem& p, bool beta0, BoxPlan* out, bool batched) {
+    if (p.family != TTX_FAMILY_MOVED && p.family != TTX_FAMILY_PRESERVED &&
+        !(batched && p.family == TTX_FAMILY_FLAT))
+        return false;
     if (p.dim[0].sa != 1 || p.dim[p.perm[0]].sb != 1) return false;
     // offsets inside a box are unsigned 32-bit byte offsets
     if (p.extent_a >= (int64_t(1) << 32) || p.extent_b >= (int64_t(1) << 32)) return false;
     Box best;
     double least = 1e300;
     each_box(p, [&](const Box& b) {
+        if (batched && !small_box(p, b)) return;
         const double c = box_cost(p, beta0, b);
         if (c < least) least = c, best = b;
     });

@@ -36,4 +36,11 @@ hipError_t launch_box(const Problem& p, const BoxPlan& bp, bool beta0, const voi
     }
 }
 
+hipError_t launch_box_batch(const BoxBatchDesc* desc, const uint32_t* first, const uint32_t* bucket,
+                            const BoxBatchGrid& g, hipStream_t stream) {
+    hipLaunchKernelGGL(k_box_batch, dim3(g.grid), dim3(kThreads), 0, stream, desc, first, bucket, g.shift, g.chunk,
+                       g.chunks);
+    return hipGetLastError();
+}
+
 }  // namespace ttx

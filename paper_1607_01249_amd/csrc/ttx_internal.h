@@ -252,6 +252,12 @@ std::string kernel_name(const Problem& p, const ttx_config& c, bool beta0, const
 
 // Box tiles (box_plan.cpp, kernels_box.hip).
 struct BoxPlan;
+struct BoxBatchDesc;
+struct BoxBatchGrid;
+// The boxes of many problems: `first` holds each one's first chunk, `bucket`
+// the problem that holds the first chunk of every 2^shift (device memory).
+hipError_t launch_box_batch(const BoxBatchDesc* desc, const uint32_t* first, const uint32_t* bucket,
+                            const BoxBatchGrid& g, hipStream_t stream);
 hipError_t launch_box(const Problem& p, const BoxPlan& bp, bool beta0, const void* A, const void* Bsrc, void* Bdst,
                       const Scalar& alpha, const Scalar& beta, hipStream_t stream);
 

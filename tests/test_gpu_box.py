@@ -64,6 +64,32 @@ def test_per_call_matches_tile_kernels_and_oracle(types, beta_zero):
             assert_parity(got, ref, False, (perm, size, pad_a))
 
 
+@pytest.mark.parametrize("copies", [1, 7], ids=["few_boxes", "more_boxes"])
+def test_batch_of_boxes_matches_plans(copies):
+    """The launch over many problems (problems of one box and of many, flat
+    ones, leading dimensions, pointers off 16-byte boundaries; chunks of one
+    box and of several) gives each problem the bytes that a plan gives it."""
+    shapes = [x for x in SHAPES for _ in range(copies)]
+    shapes += [((0,), (5,), None, None), ((0, 1), (129, 77), None, None), ((1, 0), (3, 3), None, None)]
+    keep, problems, want = [], [], []
+    for i, (perm, size, oa, ob) in enumerate(shapes):
+        dtype, beta, pad = (F32, F64)[i % 2], (0.0, 0.7, -0.25)[i % 3], i % 4
+        A, B = _inputs(perm, size, dtype, dtype, oa, ob, i)
+        want.append(gpu_transpose(perm, size, 1.3, A, beta, B, oa, ob, pad, pad,
+                                  plan_config=_described(perm, size, dtype, dtype, oa, ob, beta == 0)))
+        (dA, pa), (dB, pb) = to_device(A, pad), to_device(B, pad)
+        keep.append((dA, dB, pad))
+        problems.append(ttx.make_problem(dtype_code(dtype), perm, size, 1.3, pa, beta, pb, oa, ob))
+    batch = ttx.ttx_batch_create(problems)
+    try:
+        ttx.ttx_batch_execute(batch, ttx.current_stream())
+        for i, (_, dB, pad) in enumerate(keep):
+            got = from_device(dB, pad)
+            assert np.array_equal(got.view(np.uint8), want[i].view(np.uint8)), shapes[i]
+    finally:
+        ttx.ttx_batch_destroy(batch)
+
+
 def test_values_that_are_not_numbers_pass_through():
     """beta = 0 reads nothing of B; infinities and NaN of A arrive unchanged
     with alpha = 1 (bit for bit)."""
