@@ -261,13 +261,16 @@ ttx_status ttx_plan_kernel_name(const ttx_plan *plan, double beta, const void *A
  * A solution generated by the paper's compiler carries the sizes of its
  * transposition as compile-time constants (known trip counts); the
  * pre-instantiated kernels here take them as run-time arguments instead.
- * ttx_plan_specialise compiles, at run time with hipRTC, the plan's kernel
- * for one beta class (beta_is_zero = 1: beta == 0) with every extent,
- * stride, tile count and index divisor of the plan's problem and config as
- * a constant, and loads it on the current device.  When the tune table
- * holds a configuration tuned for specialised execution of the problem
- * (ttx_tune_specialised) and no config was set on the plan, the plan takes
- * it for that beta class first.
+ * ttx_plan_specialise compiles, at run time with hipRTC, a kernel for one
+ * beta class (beta_is_zero = 1: beta == 0) with every extent, stride, tile
+ * count and index divisor of the plan's problem as a constant, and loads it on
+ * the current device.  When the tune table holds a configuration tuned for
+ * specialised execution of the problem (ttx_tune_specialised) and no config
+ * was set on the plan, the plan takes it for that beta class and its tile
+ * kernel is compiled, as it is for a config that was set or that the tune
+ * table holds for generic execution.  Otherwise the kernel of the problem's
+ * box tiles is compiled (see ttx_transpose; "ttx_jit_..._box..."), where it
+ * has them; the plan's config is then what it runs without that kernel.
  *   reps == 0: the kernel is attached to the plan;
  *   reps > 0:  the generic and the specialised kernel are timed on scratch
  *              tensors the call allocates (minimum of `reps` runs each,
@@ -277,8 +280,8 @@ ttx_status ttx_plan_kernel_name(const ttx_plan *plan, double beta, const void *A
  * *kept (may be NULL) receives 1 when a kernel was attached.  Later
  * executions of the plan in that beta class, on that device, launch it
  * when the tensors are aligned as for the plan's vector paths (16 bytes
- * suffices; hipMalloc'd tensors are); other executions use the generic
- * kernel.  Both compute the same bits.  Moved- and preserved-family
+ * suffices; hipMalloc'd tensors are; kernels of box tiles take any alignment);
+ * other executions use the generic kernel.  Both compute the same bits.  Moved- and preserved-family
  * problems only: for empty and single-index problems nothing is attached
  * (TTX_OK, no GPU call).  A call replaces the plan's earlier specialised
  * kernel of that beta class; ttx_plan_set_config drops it.  Kernels stay
@@ -303,8 +306,9 @@ ttx_status ttx_set_auto_specialise(int calls);
  * number of cached shapes, *specialised (may be NULL) how many of them have a
  * size-specialised kernel.  Host only. */
 ttx_status ttx_transpose_cache_info(int *plans, int *specialised);
-/* The translation unit ttx_plan_specialise compiles for the plan (host
- * only), NUL-terminated into buf (len bytes).  TTX_EINVAL when buf is too
+/* The translation unit of the plan's specialised kernel: that of its box
+ * tiles once ttx_plan_specialise has attached it, else that of the tile kernel
+ * of the plan's config (host only); NUL-terminated into buf (len bytes).  TTX_EINVAL when buf is too
  * small (about 8 KB suffices) or the problem has nothing to specialise. */
 ttx_status ttx_plan_specialised_source(const ttx_plan *plan, int beta_is_zero, char *buf, int len);
 

@@ -38,7 +38,7 @@ def _compile(src):
 
 # Headers compiled at run time for size-specialised kernels (hipRTC), in
 # the order they are handed to it.
-JIT_HEADERS = ["device_types.h", "tile_kernels.h"]
+JIT_HEADERS = ["device_types.h", "tile_kernels.h", "box.h", "box_kernel.h"]
 
 
 def _embed_jit_headers():

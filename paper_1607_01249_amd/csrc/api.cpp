@@ -18,7 +18,7 @@
 struct PlanExec {
     ttx_config cfg;
     int from_table;
-    const ttx::JitKernel* jit;   // owned by the JIT cache (lives until the process ends)
+    const ttx::JitKernel* jit;   // owned by the JIT cache (lives until the process ends); of `box` where there is one
     std::shared_ptr<const ttx::BoxPlan> box;   // box tiles, run in place of cfg
 };
 
@@ -124,7 +124,13 @@ static ttx_status execute(const ttx_plan* plan, const Scalar& alpha, const void*
     ttx_status st = check_pointers(p, A, Bin, Bout, beta0);
     if (st != TTX_OK) return st;
     const std::shared_ptr<const PlanExec> x = plan->load(beta0 ? 1 : 0);
-    if (x->jit) {
+    if (x->jit && x->box) {
+        if (jit_on_device(*x->jit)) {
+            const hipError_t e = jit_box_launch(*x->jit, p, *x->box, A, beta0 ? nullptr : Bin, Bout, alpha, beta, stream);
+            if (e != hipSuccess) return fail(TTX_EHIP, std::string("kernel launch: ") + hipGetErrorString(e));
+            return TTX_OK;
+        }
+    } else if (x->jit) {
         TiledLaunch L;
         if (prepare_tiled(p, x->cfg, beta0, A, Bin, Bout, alpha, beta, &L) && jit_matches(*x->jit, L)) {
             const hipError_t e = jit_launch(*x->jit, L, stream);
@@ -133,8 +139,9 @@ static ttx_status execute(const ttx_plan* plan, const Scalar& alpha, const void*
         }
     }
     const void* Bsrc = beta0 ? nullptr : Bin;
-    const hipError_t e = x->box ? launch_box(p, *x->box, beta0, A, Bsrc, Bout, alpha, beta, stream)
-                                : launch_tiles(p, x->cfg, beta0, A, Bsrc, Bout, alpha, beta, stream);
+    const hipError_t e = x->box && plan->per_call
+                             ? launch_box(p, *x->box, beta0, A, Bsrc, Bout, alpha, beta, stream)
+                             : launch_tiles(p, x->cfg, beta0, A, Bsrc, Bout, alpha, beta, stream);
     if (e != hipSuccess) return fail(TTX_EHIP, std::string("kernel launch: ") + hipGetErrorString(e));
     return TTX_OK;
 }
@@ -348,7 +355,10 @@ ttx_status ttx_plan_specialise(ttx_plan* plan, int beta_is_zero, int reps, int* 
         generic_from_table = table_lookup(plan->prob, z == 1, &c) ? 1 : 0;
         generic = generic_from_table ? c : default_config(plan->prob);
     }
-    plan->publish(z, generic, generic_from_table, nullptr, generic_from_table ? nullptr : prev->box);
+    const std::shared_ptr<const BoxPlan> none;
+    const std::shared_ptr<const BoxPlan> box =
+        plan->user_set[z] || generic_from_table ? none : choose_box(plan->prob, z == 1);
+    plan->publish(z, generic, generic_from_table, nullptr, plan->per_call ? box : none);
     if (plan->prob.family != TTX_FAMILY_MOVED && plan->prob.family != TTX_FAMILY_PRESERVED) return TTX_OK;
     // a configuration tuned for specialised execution, when the table has one
     // and the caller has not set the config
@@ -359,45 +369,62 @@ ttx_status ttx_plan_specialise(ttx_plan* plan, int beta_is_zero, int reps, int* 
         cfg = cs;
         from_table = 1;
     }
+    // without a configuration set or tuned for it, the problem's boxes: see choose_box
+    const bool boxed = box && !from_table;
     TiledLaunch L;
-    ttx_status st = specialised_launch(plan->prob, cfg, z, &L);
+    const JitKernel *k = nullptr, *kb = nullptr;
+    ttx_status st = TTX_OK;
+    if (boxed) st = jit_box_kernel(plan->prob, *box, z == 1, &kb);
     if (st != TTX_OK) return st;
-    const JitKernel* k = nullptr;
-    st = jit_kernel(L, &k);
-    if (st != TTX_OK) return st;
+    if (!boxed || reps > 0) {
+        st = specialised_launch(plan->prob, cfg, z, &L);
+        if (st == TTX_OK) st = jit_kernel(L, &k);
+        if (st != TTX_OK) return st;
+    }
     if (reps > 0) {
-        // candidate 0: the generic kernel with its own configuration, 1: the
-        // specialised one, on the tuner's scratch tensors (hipMalloc'd, so in
-        // the compiled alignment class)
+        // candidate 0: what the plan runs without a specialised kernel, 1: the
+        // specialised tile kernel, 2: the specialised box kernel, on the
+        // tuner's scratch tensors (hipMalloc'd, so in the compiled alignment
+        // class)
         const Problem& p = plan->prob;
         const bool beta0 = z == 1;
         const Scalar alpha(1.25), beta(beta0 ? 0.0 : 0.75);
         auto launch = [&](int i, const void* A, void* B, hipStream_t stream) -> hipError_t {
             const void* Bsrc = beta0 ? nullptr : B;
+            if (i == 0 && box && plan->per_call) return launch_box(p, *box, beta0, A, Bsrc, B, alpha, beta, stream);
             if (i == 0) return launch_tiles(p, generic, beta0, A, Bsrc, B, alpha, beta, stream);
+            if (i == 2) return jit_box_launch(*kb, p, *box, A, Bsrc, B, alpha, beta, stream);
             TiledLaunch T;
             if (!prepare_tiled(p, cfg, beta0, A, Bsrc, B, alpha, beta, &T) || !jit_matches(*k, T))
                 return hipErrorInvalidValue;
             return jit_launch(*k, T, stream);
         };
         int best = 0;
-        double best_us = 0, us[2] = {0, 0};
-        st = time_candidates(p, beta0, 2, reps, launch, &best, &best_us, us);
+        double best_us = 0, us[3] = {0, 0, 0};
+        st = time_candidates(p, beta0, boxed ? 3 : 2, reps, launch, &best, &best_us, us);
         if (st != TTX_OK) return st;
         // not faster: the plan keeps its generic kernel and configuration
-        if (!(us[1] < us[0] * (1.0 - kSpecialiseMargin))) return TTX_OK;
+        if (!(best > 0 && us[best] < us[0] * (1.0 - kSpecialiseMargin))) return TTX_OK;
+        if (best == 1) kb = nullptr;
     }
-    plan->publish(z, cfg, from_table, k);
+    if (kb) plan->publish(z, generic, generic_from_table, kb, box);
+    else plan->publish(z, cfg, from_table, k);
     if (kept) *kept = 1;
     return TTX_OK;
 }
 
 ttx_status ttx_plan_specialised_source(const ttx_plan* plan, int beta_is_zero, char* buf, int len) {
     if (!plan || !buf || len <= 0) return fail(TTX_EINVAL, "NULL argument");
-    TiledLaunch L;
-    ttx_status st = specialised_launch(plan->prob, plan->load(beta_is_zero ? 1 : 0)->cfg, beta_is_zero, &L);
-    if (st != TTX_OK) return st;
-    const std::string src = jit_source(L);
+    const std::shared_ptr<const PlanExec> x = plan->load(beta_is_zero ? 1 : 0);
+    std::string src;
+    if (x->jit && x->box) {
+        src = jit_box_source(plan->prob, *x->box, beta_is_zero != 0);
+    } else {
+        TiledLaunch L;
+        ttx_status st = specialised_launch(plan->prob, x->cfg, beta_is_zero, &L);
+        if (st != TTX_OK) return st;
+        src = jit_source(L);
+    }
     if (int64_t(src.size()) >= int64_t(len)) return fail(TTX_EINVAL, "buffer too small");
     std::memcpy(buf, src.c_str(), src.size() + 1);
     return TTX_OK;
@@ -411,7 +438,9 @@ ttx_status ttx_plan_kernel_name(const ttx_plan* plan, double beta, const void* A
     const std::shared_ptr<const PlanExec> x = plan->load(beta0 ? 1 : 0);
     std::string name;
     TiledLaunch L;
-    if (x->jit && prepare_tiled(p, x->cfg, beta0, A, B, const_cast<void*>(B), Scalar(1.0), Scalar(beta), &L) &&
+    if (x->jit && x->box && jit_on_device(*x->jit))
+        name = jit_name(*x->jit);
+    else if (x->jit && !x->box && prepare_tiled(p, x->cfg, beta0, A, B, const_cast<void*>(B), Scalar(1.0), Scalar(beta), &L) &&
         jit_matches(*x->jit, L))
         name = jit_name(*x->jit);
     else

@@ -12,7 +12,9 @@
 // number of units ends with a unit that overlaps the one before it.
 #pragma once
 
+#ifndef __HIPCC_RTC__
 #include <cstdint>
+#endif
 
 #include "device_types.h"
 
@@ -205,12 +207,14 @@ struct BoxUnits {
 };
 
 template <typename T, typename S = T>
-struct BoxArgs : BoxShape {
+struct BoxPtrs {
     const S* A;
     const T* Bsrc;
     T* Bdst;
     T alpha, beta;
 };
+template <typename T, typename S = T>
+struct BoxArgs : BoxShape, BoxPtrs<T, S> {};
 
 // LDS elements of a box of B's type: 4 KiB per unit and thread, and room for
 // the padding of its runs.

@@ -9,17 +9,17 @@ namespace ttx {
 // One tile whose runs are shorter than a unit: element by element in B's
 // order, without LDS.
 template <typename T, bool BETA0, typename S>
-__device__ void box_elements(const BoxArgs<T, S>& a, const BoxCoord& c) {
+__device__ __forceinline__ void box_elements(const BoxShape& s, const BoxPtrs<T, S>& a, const BoxCoord& c) {
     int n = 1;
-    for (int k = 0; k < a.nB; ++k) n *= BoxUnits<1, 1>::extent(a.dB[k], c);
+    for (int k = 0; k < s.nB; ++k) n *= BoxUnits<1, 1>::extent(s.dB[k], c);
     for (int e = threadIdx.x; e < n; e += kThreads) {
         uint32_t v = uint32_t(e);
         int64_t oa = c.oa, ob = c.ob;
-        for (int k = 0; k < a.nB; ++k) {
-            const uint32_t ext = uint32_t(BoxUnits<1, 1>::extent(a.dB[k], c)), q = v / ext, x = v - q * ext;
+        for (int k = 0; k < s.nB; ++k) {
+            const uint32_t ext = uint32_t(BoxUnits<1, 1>::extent(s.dB[k], c)), q = v / ext, x = v - q * ext;
             v = q;
-            oa += int64_t(x) * a.dB[k].sa;
-            ob += int64_t(x) * a.dB[k].sb;
+            oa += int64_t(x) * s.dB[k].sa;
+            ob += int64_t(x) * s.dB[k].sb;
         }
         T b{};
         if constexpr (!BETA0) b = a.Bsrc[ob];
@@ -63,25 +63,24 @@ __device__ __forceinline__ void touch(const Args& a) {
 }
 
 // Box t.
-template <typename T, typename S, bool BETA0, int NU, typename Args>
-__device__ __forceinline__ void box_body(T* lds, const Args& a, uint32_t t) {
+template <typename T, typename S, bool BETA0, int NU>
+__device__ __forceinline__ void box_body(T* lds, const BoxShape& s, const BoxPtrs<T, S>& a, uint32_t t) {
     constexpr int UA = kVec<S>, UB = kVec<T>;
-    touch(a);
-    const BoxCoord c = box_coord(a, t);
+    const BoxCoord c = box_coord(s, t);
     BoxUnits<UA, UB, NU> u;
-    u.init(a, threadIdx.x, c);
-    if (u.shorter) return box_elements<T, BETA0, S>(a, c);
+    u.init(s, threadIdx.x, c);
+    if (u.shorter) return box_elements<T, BETA0, S>(s, a, c);
     const S* A = a.A + c.oa;
     vec_t<S, UA> va[NU];
     vec_t<T, UB> vb[NU];
+    // every unit is loaded, also the repeats past the last one (one request a
+    // wavefront): loads under a branch would each be waited for at its end
 #pragma unroll
-    for (int i = 0; i < NU; ++i)
-        if (kThreads * i < u.nua) ld_part<S, UA>(va[i], box_at(A, u.rel_a[i]), UA);
+    for (int i = 0; i < NU; ++i) ld_part<S, UA>(va[i], box_at(A, u.rel_a[i]), UA);
     if constexpr (!BETA0) {
         const T* B = a.Bsrc + c.ob;
 #pragma unroll
-        for (int i = 0; i < NU; ++i)
-            if (kThreads * i < u.nub) ld_part<T, UB>(vb[i], box_at(B, u.rel_b[i]), UB);
+        for (int i = 0; i < NU; ++i) ld_part<T, UB>(vb[i], box_at(B, u.rel_b[i]), UB);
     }
     bool whole = false;
     if constexpr (std::is_same<T, S>::value) {
@@ -129,7 +128,8 @@ __device__ __forceinline__ void box_body(T* lds, const Args& a, uint32_t t) {
 template <typename T, typename S, bool BETA0, int NU>
 __global__ __launch_bounds__(kThreads, 5) void k_box(BoxArgs<T, S> a) {
     __shared__ __align__(16) T lds[box_lds(sizeof(T), NU)];
-    box_body<T, S, BETA0, NU>(lds, a, box_id(blockIdx.x, a.ntiles, a.chunk));
+    touch(a);
+    box_body<T, S, BETA0, NU>(lds, a, a, box_id(blockIdx.x, a.ntiles, a.chunk));
 }
 
 // The boxes of many problems in one launch.  Every problem has whole chunks of
@@ -156,12 +156,13 @@ __global__ __launch_bounds__(kThreads, 8) inline void k_box_batch(const BoxBatch
     typedef __attribute__((address_space(4))) const BoxBatchDesc ConstDesc;
     const BoxBatchDesc& d = *(const BoxBatchDesc*)((ConstDesc*)(desc + lo));
     const uint32_t t = ((c - first[lo]) << chunk) + (r >> 3);
+    touch(d);
     if (t >= d.f64.ntiles) return;   // the last chunk's tail (both kinds start with BoxShape)
     switch (d.kind) {
-        case 0: return box_body<float, float, false, 2>(reinterpret_cast<float*>(lds), d.f32, t);
-        case 1: return box_body<float, float, true, 2>(reinterpret_cast<float*>(lds), d.f32, t);
-        case 2: return box_body<double, double, false, 2>(reinterpret_cast<double*>(lds), d.f64, t);
-        default: return box_body<double, double, true, 2>(reinterpret_cast<double*>(lds), d.f64, t);
+        case 0: return box_body<float, float, false, 2>(reinterpret_cast<float*>(lds), d.f32, d.f32, t);
+        case 1: return box_body<float, float, true, 2>(reinterpret_cast<float*>(lds), d.f32, d.f32, t);
+        case 2: return box_body<double, double, false, 2>(reinterpret_cast<double*>(lds), d.f64, d.f64, t);
+        default: return box_body<double, double, true, 2>(reinterpret_cast<double*>(lds), d.f64, d.f64, t);
     }
 }
 

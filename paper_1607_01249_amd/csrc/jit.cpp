@@ -28,6 +28,7 @@
 #include <sys/stat.h>
 #include <unistd.h>
 
+#include "box.h"
 #include "ttx_internal.h"
 #include "ttx_jit_headers.inc"   // kJitHeaderNames, kJitHeaderSources, kJitHeaderCount (generated)
 
@@ -91,6 +92,23 @@ std::string jit_entry_name(const TiledLaunch& L) {
     return n + h;
 }
 
+// `bytes` as the constant object `kHost` of type `type`.
+static std::string constant_image(const char* type, const unsigned char* bytes, size_t n) {
+    std::string s;
+    s.reserve(n * 5 + 512);
+    s += std::string("namespace {\n// the bytes of the problem's ") + type + "\nstruct Image {\n    unsigned char b[";
+    s += std::to_string(n) + "];\n};\nconstexpr Image kImage = {{";
+    char num[8];
+    for (size_t i = 0; i < n; ++i) {
+        if (i % 24 == 0) s += "\n   ";
+        std::snprintf(num, sizeof(num), " %u,", unsigned(bytes[i]));
+        s += num;
+    }
+    s += std::string("\n}};\nstatic_assert(sizeof(Image) == sizeof(") + type + "), \"argument layout\");\n";
+    s += std::string("constexpr ") + type + " kHost = __builtin_bit_cast(" + type + ", kImage);\n}  // namespace\n\n";
+    return s;
+}
+
 std::string jit_source(const TiledLaunch& L) {
     const std::string T = element_type_name(L.p.dtype), S = element_type_name(L.p.dtype_a);
     const char* b0 = L.beta0 ? "true" : "false";
@@ -130,16 +148,7 @@ std::string jit_source(const TiledLaunch& L) {
     std::string s;
     s.reserve(8192);
     s += "// size-specialised transposition kernel\n#include \"tile_kernels.h\"\n\n";
-    s += "namespace {\n// the bytes of the problem's ttx::TileArgsHost\nstruct Image {\n    unsigned char b[";
-    s += std::to_string(sizeof(TileArgsHost)) + "];\n};\nconstexpr Image kImage = {{";
-    char num[8];
-    for (size_t i = 0; i < sizeof(TileArgsHost); ++i) {
-        if (i % 24 == 0) s += "\n   ";
-        std::snprintf(num, sizeof(num), " %u,", unsigned(L.args[i]));
-        s += num;
-    }
-    s += "\n}};\nstatic_assert(sizeof(Image) == sizeof(ttx::TileArgsHost), \"argument layout\");\n";
-    s += "constexpr ttx::TileArgsHost kHost = __builtin_bit_cast(ttx::TileArgsHost, kImage);\n}  // namespace\n\n";
+    s += constant_image("ttx::TileArgsHost", L.args, sizeof(TileArgsHost));
     s += "extern \"C\" __global__ __launch_bounds__(" + std::to_string(nt) + ")";
     if (waves) s += " __attribute__((amdgpu_waves_per_eu(" + std::to_string(waves) + ")))";
     s += "\nvoid " + jit_entry_name(L) + "(ttx::TileArgs<" + T + ", " + S + "> a) {\n";
@@ -152,6 +161,42 @@ std::string jit_source(const TiledLaunch& L) {
     return s;
 }
 
+
+// The same for a box kernel: the types, the beta class, the units a thread
+// and the bytes of the box's shape.
+static std::string box_key(const Problem& p, const BoxPlan& bp, bool beta0) {
+    const int head[] = {-1, p.code, beta0 ? 1 : 0, bp.units};
+    std::string k(reinterpret_cast<const char*>(head), sizeof(head));
+    k.append(reinterpret_cast<const char*>(&bp.s), sizeof(BoxShape));
+    return k;
+}
+
+static std::string box_entry_name(const Problem& p, const BoxPlan& bp, bool beta0) {
+    auto type = [](int dtype) {
+        std::string t = element_type_name(dtype);
+        return t.rfind("ttx::", 0) == 0 ? t.substr(5) : t;
+    };
+    std::string n = std::string("ttx_jit_") + (p.family == TTX_FAMILY_MOVED ? "moved_" : "preserved_") + type(p.dtype);
+    if (p.dtype_a != p.dtype) n += "_" + type(p.dtype_a);
+    n += beta0 ? "_b0_box" : "_b_box";
+    n += std::to_string(bp.s.wA * bp.s.tA) + "x" + std::to_string(bp.s.wB * bp.s.tB);
+    const std::string key = box_key(p, bp, beta0);
+    char h[16];
+    std::snprintf(h, sizeof(h), "_%08x", unsigned(fnv1a(key.data(), key.size()) & 0xffffffffu));
+    return n + h;
+}
+
+std::string jit_box_source(const Problem& p, const BoxPlan& bp, bool beta0) {
+    const std::string T = element_type_name(p.dtype), S = element_type_name(p.dtype_a);
+    std::string s = "// size-specialised transposition kernel (box tiles)\n#include \"box_kernel.h\"\n\n";
+    s += constant_image("ttx::BoxShape", reinterpret_cast<const unsigned char*>(&bp.s), sizeof(BoxShape));
+    s += "extern \"C\" __global__ __launch_bounds__(" + std::to_string(kThreads) + ", 5)\nvoid ";
+    s += box_entry_name(p, bp, beta0) + "(ttx::BoxPtrs<" + T + ", " + S + "> a) {\n";
+    s += "    __shared__ __align__(16) " + T + " lds[ttx::box_lds(sizeof(" + T + "), " + std::to_string(bp.units) + ")];\n";
+    s += "    ttx::box_body<" + T + ", " + S + (beta0 ? ", true, " : ", false, ") + std::to_string(bp.units);
+    s += ">(lds, kHost, a, ttx::box_id(blockIdx.x, kHost.ntiles, kHost.chunk));\n}\n";
+    return s;
+}
 
 static std::string device_arch(int dev) {
     hipDeviceProp_t prop;
@@ -231,11 +276,15 @@ static std::mutex g_jit_mu;
 // Kernels live until the process ends (plans hold plain pointers to them).
 static std::map<std::pair<int, std::string>, std::unique_ptr<JitKernel>> g_jit;
 
-ttx_status jit_kernel(const TiledLaunch& L, const JitKernel** out) {
+// Finds the kernel `key` on the current device, or compiles source() and loads
+// its entry `name`.  persistent: the workgroups of `threads` that fill the
+// device are counted.
+template <typename Source>
+static ttx_status find_or_compile(const std::string& key, const std::string& name, int threads, bool persistent,
+                                  Source&& source, const JitKernel** out) {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return fail(TTX_EHIP, std::string("hipGetDevice: ") + hipGetErrorString(e));
-    const std::string key = jit_key(L);
     std::lock_guard<std::mutex> lock(g_jit_mu);
     auto it = g_jit.find({dev, key});
     if (it != g_jit.end()) {
@@ -244,7 +293,7 @@ ttx_status jit_kernel(const TiledLaunch& L, const JitKernel** out) {
     }
     const std::string arch = device_arch(dev);
     if (arch.empty()) return fail(TTX_EHIP, "cannot read the device architecture");
-    const std::string src = jit_source(L);
+    const std::string src = source();
     const std::string path = cache_file(arch, src);
     std::string code;
     const bool from_disk = !path.empty() && read_file(path, &code);
@@ -259,7 +308,7 @@ ttx_status jit_kernel(const TiledLaunch& L, const JitKernel** out) {
     std::unique_ptr<JitKernel> k(new JitKernel());
     k->device = dev;
     k->key = key;
-    k->name = jit_entry_name(L);
+    k->name = name;
     e = hipModuleLoadData(&k->module, code.data());
     if (e != hipSuccess && from_disk) {   // a damaged cache file: compile again
         ttx_status st = compile(src, arch, &code);
@@ -274,9 +323,9 @@ ttx_status jit_kernel(const TiledLaunch& L, const JitKernel** out) {
         return fail(TTX_EHIP, std::string("hipModuleGetFunction: ") + hipGetErrorString(e));
     }
     k->dense_grid = 0;
-    if (L.kind == kTileDense || (L.c.flags & TTX_CFG_PIPELINED)) {
+    if (persistent) {
         int nb = 0, cus = 0;
-        if (hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k->fn, L.c.threads, 0) != hipSuccess || nb <= 0)
+        if (hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k->fn, threads, 0) != hipSuccess || nb <= 0)
             nb = 4;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
             cus = 256;
@@ -285,6 +334,46 @@ ttx_status jit_kernel(const TiledLaunch& L, const JitKernel** out) {
     *out = k.get();
     g_jit[{dev, key}] = std::move(k);
     return TTX_OK;
+}
+
+ttx_status jit_kernel(const TiledLaunch& L, const JitKernel** out) {
+    return find_or_compile(jit_key(L), jit_entry_name(L), L.c.threads,
+                           L.kind == kTileDense || (L.c.flags & TTX_CFG_PIPELINED), [&] { return jit_source(L); }, out);
+}
+
+ttx_status jit_box_kernel(const Problem& p, const BoxPlan& bp, bool beta0, const JitKernel** out) {
+    return find_or_compile(box_key(p, bp, beta0), box_entry_name(p, bp, beta0), kThreads, false,
+                           [&] { return jit_box_source(p, bp, beta0); }, out);
+}
+
+bool jit_on_device(const JitKernel& k) {
+    int dev = 0;
+    return hipGetDevice(&dev) == hipSuccess && dev == k.device;
+}
+
+template <typename T, typename S>
+static hipError_t box_launch_as(const JitKernel& k, uint32_t grid, const void* A, const void* Bsrc, void* Bdst,
+                                const Scalar& alpha, const Scalar& beta, hipStream_t stream) {
+    BoxPtrs<T, S> a = {static_cast<const S*>(A), static_cast<const T*>(Bsrc), static_cast<T*>(Bdst),
+                       scalar_as<T>(alpha), scalar_as<T>(beta)};
+    void* params[] = {&a};
+    return hipModuleLaunchKernel(k.fn, grid, 1, 1, kThreads, 1, 1, 0, stream, params, nullptr);
+}
+
+hipError_t jit_box_launch(const JitKernel& k, const Problem& p, const BoxPlan& bp, const void* A, const void* Bsrc,
+                          void* Bdst, const Scalar& alpha, const Scalar& beta, hipStream_t stream) {
+    const uint32_t g = bp.s.ntiles;
+    switch (p.code) {
+        case TTX_F32: return box_launch_as<float, float>(k, g, A, Bsrc, Bdst, alpha, beta, stream);
+        case TTX_F64: return box_launch_as<double, double>(k, g, A, Bsrc, Bdst, alpha, beta, stream);
+        case TTX_C32: return box_launch_as<cf32, cf32>(k, g, A, Bsrc, Bdst, alpha, beta, stream);
+        case TTX_C64: return box_launch_as<cf64, cf64>(k, g, A, Bsrc, Bdst, alpha, beta, stream);
+        case TTX_F32_F64: return box_launch_as<double, float>(k, g, A, Bsrc, Bdst, alpha, beta, stream);
+        case TTX_F64_F32: return box_launch_as<float, double>(k, g, A, Bsrc, Bdst, alpha, beta, stream);
+        case TTX_C32_C64: return box_launch_as<cf64, cf32>(k, g, A, Bsrc, Bdst, alpha, beta, stream);
+        case TTX_C64_C32: return box_launch_as<cf32, cf64>(k, g, A, Bsrc, Bdst, alpha, beta, stream);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 const std::string& jit_name(const JitKernel& k) { return k.name; }

@@ -9,11 +9,8 @@ static hipError_t launch_box_as(const BoxPlan& bp, bool beta0, const void* A, co
                                 const Scalar& alpha, const Scalar& beta, hipStream_t stream) {
     BoxArgs<T, S> a;
     static_cast<BoxShape&>(a) = bp.s;
-    a.A = static_cast<const S*>(A);
-    a.Bsrc = static_cast<const T*>(Bsrc);
-    a.Bdst = static_cast<T*>(Bdst);
-    a.alpha = scalar_as<T>(alpha);
-    a.beta = scalar_as<T>(beta);
+    static_cast<BoxPtrs<T, S>&>(a) = {static_cast<const S*>(A), static_cast<const T*>(Bsrc), static_cast<T*>(Bdst),
+                                      scalar_as<T>(alpha), scalar_as<T>(beta)};
     const dim3 g(a.ntiles), b(kThreads);
     const auto kernel = bp.units == 2 ? (beta0 ? k_box<T, S, true, 2> : k_box<T, S, false, 2>)
                                       : (beta0 ? k_box<T, S, true, 4> : k_box<T, S, false, 4>);

@@ -243,6 +243,13 @@ bool jit_matches(const JitKernel& k, const TiledLaunch& L);
 // The kernel's name as profilers print it.
 const std::string& jit_name(const JitKernel& k);
 hipError_t jit_launch(const JitKernel& k, const TiledLaunch& L, hipStream_t stream);
+// The same for a box kernel (for pointers of any alignment).
+struct BoxPlan;
+ttx_status jit_box_kernel(const Problem& p, const BoxPlan& bp, bool beta0, const JitKernel** out);
+std::string jit_box_source(const Problem& p, const BoxPlan& bp, bool beta0);
+bool jit_on_device(const JitKernel& k);   // loaded on the current device
+hipError_t jit_box_launch(const JitKernel& k, const Problem& p, const BoxPlan& bp, const void* A, const void* Bsrc,
+                          void* Bdst, const Scalar& alpha, const Scalar& beta, hipStream_t stream);
 // C++ spelling of an element type ("float", "ttx::cf32", "ttx::f32x4", ...).
 const char* element_type_name(int dtype);
 
@@ -251,7 +258,6 @@ std::string kernel_name(const Problem& p, const ttx_config& c, bool beta0, const
                         const void* Bsrc, const void* Bdst);
 
 // Box tiles (box_plan.cpp, kernels_box.hip).
-struct BoxPlan;
 struct BoxBatchDesc;
 struct BoxBatchGrid;
 // The boxes of many problems: `first` holds each one's first chunk, `bucket`

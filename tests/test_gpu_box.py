@@ -64,6 +64,30 @@ def test_per_call_matches_tile_kernels_and_oracle(types, beta_zero):
             assert_parity(got, ref, False, (perm, size, pad_a))
 
 
+@pytest.mark.parametrize("types", [TYPES[0], TYPES[3], TYPES[4], TYPES[7]], ids=["s", "z", "sd", "zc"])
+def test_specialised_boxes_match_plans(types):
+    """The box kernel compiled for a problem (its source names the box, and it
+    takes pointers of any alignment) gives the bytes of the tile kernel."""
+    da, db = types
+    alpha, beta = _scalars(db, False)
+    for i in (0, 3, 8, 9, 11):
+        perm, size, oa, ob = SHAPES[i]
+        plan = ttx.ttx_plan_create(dtype_code(da, db), perm, size, oa, ob)
+        try:
+            assert ttx.ttx_plan_specialise(plan, False)
+            name = ttx.ttx_plan_kernel_name(plan, 0.5, 1 << 20, 3 << 20)
+            assert name.startswith("ttx_jit_") and "_box" in name, name
+            assert "ttx::BoxShape kHost" in ttx.ttx_plan_specialised_source(plan, False)
+        finally:
+            ttx.ttx_plan_destroy(plan)
+        A, B = _inputs(perm, size, da, db, oa, ob, i)
+        want = gpu_transpose(perm, size, alpha, A, beta, B, oa, ob,
+                             plan_config=_described(perm, size, da, db, oa, ob, False))
+        for pad_a, pad_b in ((0, 0), (1, 3)):
+            got = gpu_transpose(perm, size, alpha, A, beta, B, oa, ob, pad_a, pad_b, specialise=True)
+            assert np.array_equal(got.view(np.uint8), want.view(np.uint8)), (perm, size, pad_a)
+
+
 @pytest.mark.parametrize("copies", [1, 7], ids=["few_boxes", "more_boxes"])
 def test_batch_of_boxes_matches_plans(copies):
     """The launch over many problems (problems of one box and of many, flat
