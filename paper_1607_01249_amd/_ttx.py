@@ -13,6 +13,7 @@ when ``libttx.so`` is missing.  There is no fallback path.
 """
 import ctypes
 import os
+import struct
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libttx.so")
@@ -275,9 +276,40 @@ def _i64s(vals):
 
 
 # -- raw entry points -------------------------------------------------------------------
+_PACK = {f: [struct.Struct("%d%s" % (n, f)).pack for n in range(17)] for f in "iq"}
+_calls = None
+
+
+def _packed(vals, fmt):
+    """The integers as C ints ("i") or int64s ("q") in a bytes object."""
+    if vals is None:
+        return None
+    try:
+        return _PACK[fmt][len(vals)](*vals)
+    except (struct.error, TypeError, IndexError):   # not integers as they are, many, or out of range
+        return bytes(_ints(vals, ctypes.c_int if fmt == "i" else ctypes.c_int64))
+
+
+def _per_call():
+    """(ttx_transpose, ttx_transpose_c) taking the integer arrays as bytes: a
+    small call is bound by the host, and building ctypes arrays is a third of
+    its time in Python."""
+    global _calls
+    if _calls is None:
+        L = lib()
+        arrays = [ctypes.c_int, ctypes.c_int] + [ctypes.c_char_p] * 4
+        real, cx = L["ttx_transpose"], L["ttx_transpose_c"]
+        real.argtypes = arrays + [ctypes.c_double, vp, ctypes.c_double, vp, vp]
+        cx.argtypes = arrays + [ctypes.c_char_p, vp, ctypes.c_char_p, vp, vp]
+        real.restype = cx.restype = ctypes.c_int
+        _calls = real, cx
+    return _calls
+
+
 def ttx_transpose(dtype, n, perm, size, outer_a, outer_b, alpha, A, beta, B, stream=0):
-    return _check(lib().ttx_transpose(dtype, n, _ints(perm), _i64s(size), _i64s(outer_a),
-                                      _i64s(outer_b), float(alpha), A, float(beta), B, stream))
+    status = (_calls or _per_call())[0](dtype, n, _packed(perm, "i"), _packed(size, "q"), _packed(outer_a, "q"),
+                                        _packed(outer_b, "q"), float(alpha), A, float(beta), B, stream)
+    return status if status == OK else _check(status)
 
 
 def _complex2(v):
@@ -285,10 +317,15 @@ def _complex2(v):
     return (ctypes.c_double * 2)(v.real, v.imag)
 
 
+def _complex_packed(v):
+    v = complex(v)
+    return struct.pack("2d", v.real, v.imag)
+
+
 def ttx_transpose_c(dtype, n, perm, size, outer_a, outer_b, alpha, A, beta, B, stream=0):
-    return _check(lib().ttx_transpose_c(dtype, n, _ints(perm), _i64s(size), _i64s(outer_a),
-                                        _i64s(outer_b), _complex2(alpha), A, _complex2(beta), B,
-                                        stream))
+    status = (_calls or _per_call())[1](dtype, n, _packed(perm, "i"), _packed(size, "q"), _packed(outer_a, "q"),
+                                        _packed(outer_b, "q"), _complex_packed(alpha), A, _complex_packed(beta), B, stream)
+    return status if status == OK else _check(status)
 
 
 def ttx_plan_create(dtype, perm, size, outer_a=None, outer_b=None):
@@ -671,20 +708,35 @@ def current_stream():
     return torch.cuda.current_stream().cuda_stream
 
 
+_torch_side = None
+
+
+def _torch_calls():
+    """(code by the dtypes of A and B, the current stream's handle).  torch's
+    own fast call for the handle where it has one: building a Stream object for
+    every launch takes 1 us."""
+    global _torch_side
+    if _torch_side is None:
+        import torch
+        name = {F32: torch.float32, F64: torch.float64, C32: torch.complex64, C64: torch.complex128}
+        codes = {(name[a], name[b]): code for (a, b), code in CODE_OF.items()}
+        raw, device = (getattr(torch._C, k, None) for k in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+        _torch_side = codes, (lambda: raw(device())) if raw and device else current_stream
+    return _torch_side
+
+
 def transpose(A, B, perm, size, alpha=1.0, beta=0.0, outer_a=None, outer_b=None, stream=None):
     """B_{Pi(i)} <- alpha*A_i + beta*B_{Pi(i)} on device tensors used as flat
     column-major storage (Eqn. 1); asynchronous on ``stream`` (default: the
     current torch stream)."""
-    pair = (dtype_code(A), dtype_code(B))
-    if pair not in CODE_OF:
+    codes, current = _torch_side or _torch_calls()
+    code = codes.get((A.dtype, B.dtype))
+    if code is None:
+        dtype_code(A), dtype_code(B)   # raises for types that the library doesn't take
         raise TypeError("A and B must have the same dtype or differ only in precision")
-    code = CODE_OF[pair]
     if not (A.is_cuda and B.is_cuda):
         raise ValueError("A and B must be device tensors")
     if stream is None:
-        stream = current_stream()
-    if isinstance(alpha, complex) or isinstance(beta, complex):
-        return ttx_transpose_c(code, len(perm), perm, size, outer_a, outer_b, alpha, A.data_ptr(),
-                               beta, B.data_ptr(), stream)
-    return ttx_transpose(code, len(perm), perm, size, outer_a, outer_b, alpha, A.data_ptr(), beta,
-                         B.data_ptr(), stream)
+        stream = current()
+    run = ttx_transpose_c if isinstance(alpha, complex) or isinstance(beta, complex) else ttx_transpose
+    return run(code, len(perm), perm, size, outer_a, outer_b, alpha, A.data_ptr(), beta, B.data_ptr(), stream)
