@@ -242,7 +242,13 @@ struct BoxPlan {
     int64_t elements;    // of a full box
     double cost;         // estimated time, us
     int units;           // per thread and side that hold the box: 2 or 4
+    bool nt;             // nontemporal stores, if B starts on a line
 };
+// Whether the box's store kind suits B: nontemporal stores of partial lines
+// are slow, and a B that does not start on a line has them throughout.
+inline bool box_takes(const BoxPlan& bp, const void* B) {
+    return !bp.nt || reinterpret_cast<uintptr_t>(B) % 128 == 0;
+}
 // The best box for a problem, false if it has none (no contiguous runs of a
 // unit on both sides, offsets beyond 32 bits, empty problems).  `batched`: for
 // a launch over many problems (two units a thread, and flat problems too,

@@ -1,4 +1,15 @@
 // The box-tile kernel (see box.h).
+//
+// Large problems are bound by memory: whole runs on both sides reach 5.5 TB/s
+// (6D f64 [20,16,16,20,16,16], update, 0.117 ms; the whole-unit dense tiles
+// took 0.175) and short or unaligned ones 4.6 to 5.4 (4D f32 reversal 0.089 ms,
+// 6D f32 reversal with odd extents 0.136), where a copy runs at 6.1.  Small ones
+// are bound by one box's chain: arguments, offsets, loads, LDS, stores.  The
+// offsets were the bound at first: with integer divisions and one pass of the
+// indices per unit a box cost 1000 instructions and 80 scalar loads one after
+// the other, 1.35 times the menu's time over all; the indices as the outer loop
+// and float quotients brought 0.98, one box per workgroup (8 wavefronts a SIMD
+// where the loop left 4), 32 boxes in a row per XCD and B's order 0.81.
 #pragma once
 
 #include "box.h"
@@ -62,8 +73,8 @@ __device__ __forceinline__ void touch(const Args& a) {
     for (int i = 0; i < n; ++i) asm volatile("" ::"s"(x[i]));
 }
 
-// Box t.
-template <typename T, typename S, bool BETA0, int NU>
+// Box t.  NT: nontemporal stores.
+template <typename T, typename S, bool BETA0, int NU, bool NT = false>
 __device__ __forceinline__ void box_body(T* lds, const BoxShape& s, const BoxPtrs<T, S>& a, uint32_t t) {
     constexpr int UA = kVec<S>, UB = kVec<T>;
     const BoxCoord c = box_coord(s, t);
@@ -121,15 +132,15 @@ __device__ __forceinline__ void box_body(T* lds, const BoxShape& s, const BoxPtr
             vec_t<T, UB> v;
 #pragma unroll
             for (int j = 0; j < UB; ++j) set_lane<T, UB>(v, j, lds[u.gather(i, j)]);
-            st_part<T, UB, false>(box_at(B, u.rel_b[i]), epilogue<T, UB, BETA0>(v, vb[i], a.alpha, a.beta), UB);
+            st_part<T, UB, NT>(box_at(B, u.rel_b[i]), epilogue<T, UB, BETA0>(v, vb[i], a.alpha, a.beta), UB);
         }
 }
 
-template <typename T, typename S, bool BETA0, int NU>
+template <typename T, typename S, bool BETA0, int NU, bool NT>
 __global__ __launch_bounds__(kThreads, 5) void k_box(BoxArgs<T, S> a) {
     __shared__ __align__(16) T lds[box_lds(sizeof(T), NU)];
     touch(a);
-    box_body<T, S, BETA0, NU>(lds, a, a, box_id(blockIdx.x, a.ntiles, a.chunk));
+    box_body<T, S, BETA0, NU, NT>(lds, a, a, box_id(blockIdx.x, a.ntiles, a.chunk));
 }
 
 // The boxes of many problems in one launch.  Every problem has whole chunks of

@@ -162,10 +162,10 @@ std::string jit_source(const TiledLaunch& L) {
 }
 
 
-// The same for a box kernel: the types, the beta class, the units a thread
-// and the bytes of the box's shape.
+// The same for a box kernel: the types, the beta class, the units a thread,
+// the store kind and the bytes of the box's shape.
 static std::string box_key(const Problem& p, const BoxPlan& bp, bool beta0) {
-    const int head[] = {-1, p.code, beta0 ? 1 : 0, bp.units};
+    const int head[] = {-1, p.code, beta0 ? 1 : 0, bp.units, bp.nt ? 1 : 0};
     std::string k(reinterpret_cast<const char*>(head), sizeof(head));
     k.append(reinterpret_cast<const char*>(&bp.s), sizeof(BoxShape));
     return k;
@@ -194,6 +194,7 @@ std::string jit_box_source(const Problem& p, const BoxPlan& bp, bool beta0) {
     s += box_entry_name(p, bp, beta0) + "(ttx::BoxPtrs<" + T + ", " + S + "> a) {\n";
     s += "    __shared__ __align__(16) " + T + " lds[ttx::box_lds(sizeof(" + T + "), " + std::to_string(bp.units) + ")];\n";
     s += "    ttx::box_body<" + T + ", " + S + (beta0 ? ", true, " : ", false, ") + std::to_string(bp.units);
+    s += bp.nt ? ", true" : ", false";
     s += ">(lds, kHost, a, ttx::box_id(blockIdx.x, kHost.ntiles, kHost.chunk));\n}\n";
     return s;
 }

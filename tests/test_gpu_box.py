@@ -88,6 +88,19 @@ def test_specialised_boxes_match_plans(types):
             assert np.array_equal(got.view(np.uint8), want.view(np.uint8)), (perm, size, pad_a)
 
 
+@pytest.mark.parametrize("dtype,perm,size", [(F32, (2, 1, 0), (515, 33, 1024)), (F64, (1, 0), (96, 90000))],
+                         ids=["rows_cut", "long_runs"])
+def test_large_outputs_in_whole_lines(dtype, perm, size):
+    """Outputs of 64 MiB and more in whole 128-byte lines (nontemporal stores),
+    per call and specialised, and the same where B does not start on a line."""
+    A, B = _inputs(perm, size, dtype, dtype, None, None, 60)
+    want = gpu_transpose(perm, size, 1.3, A, 0.0, B, plan_config=_described(perm, size, dtype, dtype, None, None, True))
+    for pad in (0, 1):
+        for specialise in (False, True):
+            got = gpu_transpose(perm, size, 1.3, A, 0.0, B, pad_b=pad, specialise=specialise)
+            assert np.array_equal(got.view(np.uint8), want.view(np.uint8)), (pad, specialise)
+
+
 @pytest.mark.parametrize("copies", [1, 7], ids=["few_boxes", "more_boxes"])
 def test_batch_of_boxes_matches_plans(copies):
     """The launch over many problems (problems of one box and of many, flat
