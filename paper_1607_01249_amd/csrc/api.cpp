@@ -62,17 +62,22 @@ static std::shared_ptr<const BoxPlan> choose_box(const Problem& p, bool beta0) {
     return plan_box(p, beta0, bp.get()) ? bp : nullptr;
 }
 
+static void resolve_config(ttx_plan* plan, int z) {
+    ttx_config c;
+    if (table_lookup(plan->prob, z == 1, &c)) {
+        plan->publish(z, c, 1, nullptr);
+        return;
+    }
+    const std::shared_ptr<const BoxPlan> box = plan->per_call ? choose_box(plan->prob, z == 1) : nullptr;
+    std::memset(&c, 0, sizeof(c));   // not used where there is a box
+    plan->publish(z, box ? c : default_config(plan->prob), 0, nullptr, box);
+}
+
+// A per-call plan is resolved for the beta classes that calls come with (see
+// transpose_cached): a new shape costs one choice of a box.
 static void resolve_configs(ttx_plan* plan) {
     plan->table_gen = table_generation();
-    for (int z = 0; z < 2; ++z) {
-        if (plan->user_set[z]) continue;
-        ttx_config c;
-        if (table_lookup(plan->prob, z == 1, &c))
-            plan->publish(z, c, 1, nullptr);
-        else
-            plan->publish(z, default_config(plan->prob), 0, nullptr,
-                          plan->per_call ? choose_box(plan->prob, z == 1) : nullptr);
-    }
+    for (int z = 0; z < 2 && !plan->per_call; ++z) resolve_config(plan, z);
 }
 
 static ttx_status new_plan(ttx_plan** out, int dtype, int n, const int* perm, const int64_t* size,
@@ -227,6 +232,11 @@ ttx_status transpose_cached(int dtype, int n, const int* perm, const int64_t* si
         if (g_cache.size() >= kCacheCap) g_cache.clear();
         g_cache[key] = plan;
     }
+    const int z = beta_is_zero(plan->prob.dtype, beta) ? 1 : 0;
+    if (!plan->load(z)) {
+        std::lock_guard<std::mutex> lock(plan->mu);
+        if (!plan->load(z)) resolve_config(plan.get(), z);
+    }
     const int hot = auto_calls();
     if (hot > 0) maybe_specialise(plan.get(), beta, hot);
     return execute(plan.get(), alpha, A, beta, Bin, Bout, stream);
@@ -235,7 +245,10 @@ ttx_status transpose_cached(int dtype, int n, const int* perm, const int64_t* si
 static void cache_info(int* plans, int* specialised) {
     std::lock_guard<std::mutex> lock(g_cache_mu);
     int s = 0;
-    for (const auto& kv : g_cache) s += (kv.second->load(0)->jit || kv.second->load(1)->jit) ? 1 : 0;
+    for (const auto& kv : g_cache) {
+        const auto x = kv.second->load(0), y = kv.second->load(1);
+        s += ((x && x->jit) || (y && y->jit)) ? 1 : 0;
+    }
     if (plans) *plans = int(g_cache.size());
     if (specialised) *specialised = s;
 }
@@ -350,7 +363,7 @@ ttx_status ttx_plan_specialise(ttx_plan* plan, int beta_is_zero, int reps, int* 
     // the generic configuration: the one in effect without a specialised kernel
     ttx_config generic = prev->cfg;
     int generic_from_table = prev->from_table;
-    if (prev->jit && !plan->user_set[z]) {   // a specialised configuration may be in effect: look again
+    if ((prev->jit || prev->box) && !plan->user_set[z]) {   // a specialised configuration may be in effect: look again
         ttx_config c;
         generic_from_table = table_lookup(plan->prob, z == 1, &c) ? 1 : 0;
         generic = generic_from_table ? c : default_config(plan->prob);
