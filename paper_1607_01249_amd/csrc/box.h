@@ -239,8 +239,6 @@ struct BoxBatchGrid {
 // A box for one problem (host).
 struct BoxPlan {
     BoxShape s;
-    int64_t elements;    // of a full box
-    double cost;         // estimated time, us
     int units;           // per thread and side that hold the box: 2 or 4
     bool nt;             // nontemporal stores, if B starts on a line
 };
