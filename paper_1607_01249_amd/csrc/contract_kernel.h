@@ -94,7 +94,9 @@ constexpr int contract_pad(int elem, int kt) { return 64 * (16 / elem) / kt; }
 // one 16-byte load at element alignment; otherwise lanes take consecutive
 // places, U times.  Loads are unconditional: a row that does not exist has
 // the offset of row 0 and its sums are not stored; a k that does not exist is
-// read at k = 0 and becomes zero, in both operands, on its way to LDS.
+// read at k = 0 and becomes zero, in both operands, on its way to LDS; lanes
+// beyond the walk (80 columns: 20 or 40 units in a row of 32 or 64 lanes)
+// read its last place, a whole unit with VEC, and store nothing.
 template <typename T, int ROWS, int KT, bool KW, bool VEC>
 struct ContractLoad {
     static constexpr int U = 16 / int(sizeof(T));
@@ -113,14 +115,14 @@ struct ContractLoad {
 
     // rows: byte offsets of the tile's rows.  wa x wb: the walk over the first
     // `used` rows, or over k.
-    __device__ __forceinline__ void init(const T* p, const int64_t* rows, int wa, int wb, int used) {
+    __host__ __device__ __forceinline__ void init(int tid, const T* p, const int64_t* rows, int wa, int wb, int used) {
         const char* base = reinterpret_cast<const char*>(p);
-        const int u = int(threadIdx.x) % P;
-        other = int(threadIdx.x) / P;
+        int u = tid % P;
+        if (P != W && u >= W) u = W - 1;
+        other = tid / P;
 #pragma unroll
         for (int j = 0; j < U; ++j) {
             int r = VEC ? u * U + j : u + j * W;
-            if (P != W) r = min(r, (KW ? KT : ROWS) - 1);
             if (wa > 1 && r < used) {
                 const int x = r % wa, q = r / wa;
                 r = q % wb + wb * (x + wa * (q / wb));
@@ -129,7 +131,7 @@ struct ContractLoad {
         }
         if constexpr (KW) {
 #pragma unroll
-            for (int i = 0; i < N; ++i) at[i] = base + rows[min(other + i * R, ROWS - 1)];
+            for (int i = 0; i < N; ++i) at[i] = base + rows[other + i * R < ROWS ? other + i * R : ROWS - 1];
         } else {
 #pragma unroll
             for (int j = 0; j < (VEC ? 1 : U); ++j) at[j] = base + rows[place[j]];
@@ -139,30 +141,21 @@ struct ContractLoad {
     __device__ __forceinline__ bool live(int i) const {
         return (P == W || int(threadIdx.x) % P < W) && (E % R == 0 || other + i * R < E);
     }
-    __device__ __forceinline__ int k_of(int i) const { return E % R == 0 ? other + i * R : min(other + i * R, KT - 1); }
-    // koff: byte offsets of the step's k values
+    __host__ __device__ __forceinline__ int k_of(int i) const {
+        return E % R == 0 || other + i * R < KT ? other + i * R : KT - 1;
+    }
+    // Where pass i reads its unit (VEC), or place j of it.  koff: byte offsets
+    // of the step's k values
+    __host__ __device__ __forceinline__ const char* from(const int64_t* koff, int i, int j) const {
+        return KW ? at[i] + koff[place[j]] : at[VEC ? 0 : j] + koff[k_of(i)];
+    }
     __device__ __forceinline__ void load(const int64_t* koff) {
-        if constexpr (KW) {
+        constexpr int places = VEC ? 1 : U;
 #pragma unroll
-            for (int j = 0; j < (VEC ? 1 : U); ++j) {
-                const int64_t q = koff[place[j]];
-#pragma unroll
-                for (int i = 0; i < N; ++i) {
-                    if constexpr (VEC) v[i] = reinterpret_cast<const Loose*>(at[i] + q)->v;
-                    else v[i][j] = *reinterpret_cast<const T*>(at[i] + q);
-                }
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < N; ++i) {
-                const int64_t q = koff[k_of(i)];
-                if constexpr (VEC) {
-                    v[i] = reinterpret_cast<const Loose*>(at[0] + q)->v;
-                } else {
-#pragma unroll
-                    for (int j = 0; j < U; ++j) v[i][j] = *reinterpret_cast<const T*>(at[j] + q);
-                }
-            }
+        for (int n = 0; n < places * N; ++n) {
+            const int i = KW ? n % N : n / places, j = KW ? n / N : n % places;   // one k after the other
+            if constexpr (VEC) v[i] = reinterpret_cast<const Loose*>(from(koff, i, 0))->v;
+            else v[i][j] = *reinterpret_cast<const T*>(from(koff, i, j));
         }
     }
     // Zeros the k values that do not exist (gone[k] != 0).
@@ -321,8 +314,8 @@ __global__ __launch_bounds__(256) void k_contract(ContractArgs a, const T* __res
     ContractLoad<T, MT, KT, XK, VEC> lx;
     ContractLoad<T, NT, KT, YK, VEC> ly;
     const bool whole_x = a.walk_x == 1;
-    lx.init(X, row_x, XK ? 1 : a.walk_x, a.walk_y, a.rows);
-    ly.init(Y, col_y, XK && YK && a.kwalk_x > 1 ? a.kwalk_y : 1, a.kwalk_x, KT);
+    lx.init(tid, X, row_x, XK ? 1 : a.walk_x, a.walk_y, a.rows);
+    ly.init(tid, Y, col_y, XK && YK && a.kwalk_x > 1 ? a.kwalk_y : 1, a.kwalk_x, KT);
     if (steps > 0) {
         lx.load(kx);
         ly.load(ky);
@@ -515,13 +508,13 @@ __global__ __launch_bounds__(256) void k_contract_pack(ContractArgs a, const T* 
     __syncthreads();
     if (is_x) {
         ContractLoad<T, MT, KT, XK, VEC> l;
-        l.init(X, rows, XK ? 1 : a.walk_x, a.walk_y, a.rows);
+        l.init(tid, X, rows, XK ? 1 : a.walk_x, a.walk_y, a.rows);
         l.load(koff);
         l.zero(gone);
         l.store(lds, a.walk_x == 1);
     } else {
         ContractLoad<T, NT, KT, YK, VEC> l;
-        l.init(Y, rows, XK && YK && a.kwalk_x > 1 ? a.kwalk_y : 1, a.kwalk_x, KT);
+        l.init(tid, Y, rows, XK && YK && a.kwalk_x > 1 ? a.kwalk_y : 1, a.kwalk_x, KT);
         l.load(koff);
         l.zero(gone);
         l.store(lds, true);
@@ -640,8 +633,8 @@ __global__ __launch_bounds__(256) void k_contract_short(ContractArgs a, const T*
         begin_c();
         ContractLoad<T, MT, KT, XK, VEC> lx;
         ContractLoad<T, NT, KT, YK, VEC> ly;
-        lx.init(X, row_x, XK ? 1 : a.walk_x, a.walk_y, a.rows);
-        ly.init(Y, col_y, XK && YK && a.kwalk_x > 1 ? a.kwalk_y : 1, a.kwalk_x, KT);
+        lx.init(tid, X, row_x, XK ? 1 : a.walk_x, a.walk_y, a.rows);
+        ly.init(tid, Y, col_y, XK && YK && a.kwalk_x > 1 ? a.kwalk_y : 1, a.kwalk_x, KT);
         lx.load(kx);
         ly.load(ky);
         lx.zero(gone);
