@@ -84,7 +84,11 @@ struct ContractArgs {
     // columns in NT / c_cut groups (dv_cut.d) of c_cut, the groups first
     FastDiv dv_run, dv_cut;
     int c_cut;
+    uint32_t first;     // the launch's first workgroup (set by the launch)
 };
+
+// Workgroups of one launch: one of 2^32 work items and more is refused.
+constexpr int64_t kContractGroups = int64_t(1) << 23;
 
 // Tile shapes: 4 waves of 16*mb rows each, 16*nb columns.
 struct ContractVariant {

@@ -268,7 +268,8 @@ struct ContractOut {
     }
 };
 
-// Grid: tiles_m * tiles_n * splits workgroups.  With one split the tile is
+// Grid: tiles_m * tiles_n * splits workgroups, those from a.first on where
+// they take more than one launch.  With one split the tile is
 // written to C with alpha and beta; otherwise each split writes its partial
 // sums to part[((split * tiles + tile) * NT + column) * MT + row].
 //
@@ -292,7 +293,7 @@ __global__ __launch_bounds__(256) void k_contract(ContractArgs a, const T* __res
     __shared__ int64_t kx[512], ky[512];
     __shared__ uint8_t gone[512];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t id = swizzle_id(blockIdx.x, gridDim.x);
+    const uint32_t id = a.first + swizzle_id(blockIdx.x, gridDim.x);
     const uint32_t split = a.dv_tiles.div(id), tile = id - split * a.dv_tiles.d;
     const uint32_t tn = a.dv_m.div(tile), tm = tile - tn * a.dv_m.d;
     const int64_t s0 = int64_t(split) * a.split_steps;
@@ -483,7 +484,7 @@ struct ContractWalk {
 
 // The operands of a short sum as whole tiles, tile by tile, KT x rows with the
 // rows contiguous and zeros for k values that do not exist (rows that do not
-// exist hold copies of row 0): workgroup b packs X's tile b, or Y's.
+// exist hold copies of row 0): workgroup b of all packs X's tile b, or Y's.
 template <typename T, int MT, int NT, int KT, bool XK, bool YK, bool VEC>
 __global__ __launch_bounds__(256) void k_contract_pack(ContractArgs a, const T* __restrict__ X,
                                                        const T* __restrict__ Y, T* __restrict__ packed) {
@@ -494,8 +495,9 @@ __global__ __launch_bounds__(256) void k_contract_pack(ContractArgs a, const T* 
     __shared__ int64_t rows[MT > NT ? MT : NT], unused[MT > NT ? MT : NT], koff[KT];
     __shared__ uint8_t gone[KT];
     const int tid = threadIdx.x;
-    const bool is_x = blockIdx.x < a.tiles_m;
-    const int64_t tile = is_x ? blockIdx.x : blockIdx.x - a.tiles_m;
+    const int64_t id = int64_t(a.first) + blockIdx.x;
+    const bool is_x = id < a.tiles_m;
+    const int64_t tile = is_x ? id : id - a.tiles_m;
     if (is_x) contract_rows<T, MT>(a.m, tile * a.rows, a.rows, 0, rows, unused);
     else contract_rows<T, NT>(a.n, tile * NT, NT, 0, rows, unused);
     if (tid >= 256 - KT) {
@@ -597,7 +599,7 @@ __global__ __launch_bounds__(256) void k_contract_short(ContractArgs a, const T*
     T* const ys = lds + LX::elems(KT);
     __shared__ int64_t row_c[MT], col_c[NT];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t tile = swizzle_id(blockIdx.x, gridDim.x);
+    const uint32_t tile = a.first + swizzle_id(blockIdx.x, gridDim.x);
     const uint32_t tn = a.dv_m.div(tile), tm = tile - tn * a.dv_m.d;
     typename Mma<T>::Acc acc[MB][NB];
     std::conditional_t<VECC, Walk, ContractOut<T, MB, NB, false>> out;
@@ -659,14 +661,14 @@ __global__ __launch_bounds__(256) void k_contract_short(ContractArgs a, const T*
     }
 }
 
-// Sums the splits' partial sums in split order and writes C.  Workgroup b:
-// 16 columns (b % NB) of tile b / NB.
+// Sums the splits' partial sums in split order and writes C.  Workgroup b of
+// all: 16 columns (b % NB) of tile b / NB.
 template <typename T, int MB, int NB>
 __global__ __launch_bounds__(256) void k_contract_sum(ContractArgs a, const T* __restrict__ part, T* __restrict__ C,
                                                       int splits, T alpha, T beta, int beta0) {
     constexpr int MT = 64 * MB, NT = 16 * NB, N = 16 * MT / 256;
     __shared__ int64_t row_c[MT], col_c[16];
-    const uint32_t tile = blockIdx.x / NB, cb = blockIdx.x % NB;
+    const uint32_t id = a.first + blockIdx.x, tile = id / NB, cb = id % NB;
     const uint32_t tn = a.dv_m.div(tile), tm = tile - tn * a.dv_m.d;
     contract_rows<T, MT>(a.m, int64_t(tm) * a.rows, a.rows, 0, nullptr, row_c);
     contract_rows<T, 16>(a.n, int64_t(tn) * NT + 16 * cb, 16, 240, nullptr, col_c);
@@ -697,21 +699,33 @@ hipError_t launch_contract_as(const ContractPlan& p, const T* X, const T* Y, T* 
     if (tiles <= 0) return hipSuccess;
     if (p.args.tiles_m > int64_t(0x7fffffff) || tiles > int64_t(0x7fffffff) / (p.splits > NB ? p.splits : NB))
         return hipErrorInvalidValue;
-    const dim3 g{uint32_t(tiles * p.splits)}, b{256};
     T* out = p.splits > 1 ? part : nullptr;
     const int beta0 = beta == T(0);
+    ContractArgs a = p.args;
+    // launches of at most kContractGroups workgroups that come to `groups`
+    auto each = [&](int64_t groups, auto&& launch) {
+        for (int64_t first = 0; first < groups; first += kContractGroups) {
+            a.first = uint32_t(first);
+            launch(dim3(uint32_t(groups - first < kContractGroups ? groups - first : kContractGroups)));
+        }
+    };
+    const dim3 b{256};
     auto go = [&](auto xk, auto yk, auto vec) {
-        hipLaunchKernelGGL((k_contract<T, MB, NB, xk.value, yk.value, vec.value>), g, b, 0, stream, p.args, X, Y, C, out,
-                           alpha, beta, beta0);
+        each(tiles * p.splits, [&](dim3 g) {
+            hipLaunchKernelGGL((k_contract<T, MB, NB, xk.value, yk.value, vec.value>), g, b, 0, stream, a, X, Y, C, out,
+                               alpha, beta, beta0);
+        });
     };
     auto go_short = [&](auto xk, auto yk, auto vec) {
         if constexpr (contract_has_short(sizeof(T), MB, NB)) {
             constexpr int KT = contract_kt(sizeof(T), MB);
             auto with_c = [&](auto packed, auto vecc, auto update) {
                 constexpr bool P = packed.value;
-                hipLaunchKernelGGL((k_contract_short<T, MB, NB, KT, !P && xk.value, !P && yk.value, P || vec.value, P,
-                                                     vecc.value, update.value>),
-                                   g, b, 0, stream, p.args, P ? part : X, Y, C, alpha, beta);
+                each(tiles, [&](dim3 g) {
+                    hipLaunchKernelGGL((k_contract_short<T, MB, NB, KT, !P && xk.value, !P && yk.value, P || vec.value,
+                                                         P, vecc.value, update.value>),
+                                       g, b, 0, stream, a, P ? part : X, Y, C, alpha, beta);
+                });
             };
             auto with_packed = [&](auto packed) {
                 if (p.vec_c && beta0) with_c(packed, std::true_type{}, std::false_type{});
@@ -720,15 +734,17 @@ hipError_t launch_contract_as(const ContractPlan& p, const T* X, const T* Y, T* 
                 else with_c(packed, std::false_type{}, std::true_type{});
             };
             if (p.packed) {
-                hipLaunchKernelGGL((k_contract_pack<T, 64 * MB, 16 * NB, KT, xk.value, yk.value, vec.value>),
-                                   dim3(uint32_t(p.args.tiles_m + p.args.tiles_n)), b, 0, stream, p.args, X, Y, part);
+                each(a.tiles_m + a.tiles_n, [&](dim3 g) {
+                    hipLaunchKernelGGL((k_contract_pack<T, 64 * MB, 16 * NB, KT, xk.value, yk.value, vec.value>), g, b, 0,
+                                       stream, a, X, Y, part);
+                });
                 with_packed(std::true_type{});
             } else {
                 with_packed(std::false_type{});
             }
         }
     };
-    const bool is_short = contract_has_short(sizeof(T), MB, NB) && p.args.steps == 1;
+    const bool is_short = contract_has_short(sizeof(T), MB, NB) && a.steps == 1;
     auto with_vec = [&](auto xk, auto yk) {
         if (is_short && p.vec_xy) go_short(xk, yk, std::true_type{});
         else if (is_short) go_short(xk, yk, std::false_type{});
@@ -741,8 +757,9 @@ hipError_t launch_contract_as(const ContractPlan& p, const T* X, const T* Y, T* 
     else with_vec(std::false_type{}, std::false_type{});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.splits == 1) return e;
-    hipLaunchKernelGGL((k_contract_sum<T, MB, NB>), dim3(uint32_t(tiles * NB)), b, 0, stream, p.args, part, C, p.splits,
-                       alpha, beta, beta0);
+    each(tiles * NB, [&](dim3 g) {
+        hipLaunchKernelGGL((k_contract_sum<T, MB, NB>), g, b, 0, stream, a, part, C, p.splits, alpha, beta, beta0);
+    });
     return hipGetLastError();
 }
 
