@@ -28,29 +28,32 @@
 #include "box.h"
 #include "ttx_internal.h"
 
-struct ttx_batch {
-    std::vector<ttx::Problem> prob;
-    std::vector<ttx_problem> src;
-    std::vector<ttx_config> cfg;
-    std::vector<int> forced;
-    std::vector<char> described;         // cfg is filled in (problems in box tiles: when it is asked for)
+// What describe_all makes of the problems: the tables and sizes of the launches.
+struct BatchLayout {
     std::vector<int> per_call;           // problems launched with their per-call kernels
     std::vector<ttx::BatchDesc> desc;    // kernel problems, in work order
     std::vector<uint32_t> chunk_prefix;  // over the work order
     std::vector<int> order;              // work position -> problem index
     int nk = 0;                          // problems in the persistent kernel
-    bool boxes = false;                  // untuned problems run box tiles where they have them
-    std::vector<int> tuned;              // problems that keep a tuned configuration
     std::vector<ttx::BoxBatchDesc> box;  // problems in box tiles
     std::vector<uint32_t> box_first, box_bucket;   // first chunk per problem, first problem per stretch of chunks
     ttx::BoxBatchGrid box_grid{};
-    unsigned char* d_work = nullptr;     // descriptors, chunk prefix, claim counter
-    size_t work_bytes = 0;
-    size_t counter_at = size_t(-1);      // where the claim counter was cleared
     uint64_t total = 0;                  // tiles
     uint32_t chunks = 0;
     int grid = 0;
     int64_t bytes = 0;
+};
+
+struct ttx_batch : BatchLayout {
+    std::vector<ttx::Problem> prob;
+    std::vector<ttx_problem> src;
+    std::vector<ttx_config> cfg;
+    std::vector<int> forced;
+    std::vector<char> described;         // cfg is filled in (problems in box tiles: when it is asked for)
+    bool boxes = false;                  // untuned problems run box tiles where they have them
+    std::vector<int> tuned;              // problems that keep a tuned configuration
+    unsigned char* d_work = nullptr;     // the tables on the device (see block_bytes)
+    size_t counter_at = size_t(-1);      // where the claim counter was cleared
     hipStream_t cap_stream = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -502,8 +505,11 @@ static constexpr size_t work_bytes(int count) { return counter_offset(count) + 2
 // After them, in a batch that has problems in box tiles: their descriptors,
 // first chunks and the buckets.
 static size_t box_offset(const ttx_batch* b) { return (work_bytes(b->nk) + 255) & ~size_t(255); }
-static size_t box_bytes(const ttx_batch* b) {
-    return b->box.size() * (sizeof(BoxBatchDesc) + sizeof(uint32_t)) + b->box_bucket.size() * sizeof(uint32_t);
+// The work block of `count` problems in whichever of the two kernels each of
+// them runs: updates and tuning move problems between them and allocate nothing.
+static size_t block_bytes(int count) {
+    return work_bytes(count) + 256 + size_t(count) * (sizeof(BoxBatchDesc) + sizeof(uint32_t)) +
+           (kBoxBuckets + 2) * sizeof(uint32_t);
 }
 
 static const BatchDesc* work_desc(const ttx_batch* b) { return reinterpret_cast<const BatchDesc*>(b->d_work); }
@@ -526,7 +532,7 @@ static ttx_status config_of(const ttx_batch* b, int i, ttx_config* config) {
 }
 
 // Adds problem i to the launch of boxes if it has them.
-static bool add_boxes(ttx_batch* b, int i, bool beta0, uint64_t* boxes) {
+static bool add_boxes(const ttx_batch* b, int i, bool beta0, BatchLayout* out, uint64_t* boxes) {
     const ttx_problem& q = b->src[i];
     const Problem& p = b->prob[i];
     BoxPlan bp;
@@ -547,17 +553,14 @@ static bool add_boxes(ttx_batch* b, int i, bool beta0, uint64_t* boxes) {
     if (p.dtype == TTX_F32) fill(d.f32);
     else fill(d.f64);
     d.kind = (p.dtype == TTX_F32 ? 0 : 2) + (beta0 ? 1 : 0);
-    b->box.push_back(d);
+    out->box.push_back(d);
     return true;
 }
 
 // Chunks of boxes: 32 where that leaves few places empty, less for batches of
 // problems with few boxes.
-static void layout_boxes(ttx_batch* b, uint64_t boxes) {
+static void layout_boxes(BatchLayout* b, uint64_t boxes) {
     BoxBatchGrid& g = b->box_grid;
-    g = BoxBatchGrid{};
-    b->box_first.clear();
-    b->box_bucket.clear();
     if (b->box.empty()) return;
     auto chunks_of = [&](const BoxBatchDesc& d, int k) { return (d.f64.ntiles + (1u << k) - 1) >> k; };
     for (g.chunk = 5; g.chunk > 0; --g.chunk) {
@@ -586,51 +589,53 @@ static hipError_t launch_boxes(const ttx_batch* b, hipStream_t stream) {
     return launch_box_batch(desc, first, first + b->box.size(), b->box_grid, stream);
 }
 
+// Lays out the batch as its problems now are; on failure it stays as it was,
+// which is how the device's tables and a captured graph have it.
 static ttx_status describe_all(ttx_batch* b) {
     const int count = int(b->prob.size());
+    BatchLayout next;
+    std::vector<ttx_config> cfg = b->cfg;
+    std::vector<char> described = b->described;
     std::vector<BatchDesc> desc(count);
-    std::vector<int> kernel;
     uint64_t total = 0, boxes = 0;
-    b->bytes = 0;
-    b->per_call.clear();
-    b->box.clear();
     for (int i = 0; i < count; ++i) {
         const ttx_problem& q = b->src[i];
         const Problem& p = b->prob[i];
         const bool beta0 = beta_is_zero(p.dtype, beta_of(q));
-        b->bytes += p.elements * (elem_bytes(p.dtype_a) + elem_bytes(p.dtype) * (beta0 ? 1 : 2));
+        next.bytes += p.elements * (elem_bytes(p.dtype_a) + elem_bytes(p.dtype) * (beta0 ? 1 : 2));
         if (runs_per_call(p)) {
-            if (!b->forced[i] && !table_lookup(p, beta0, &b->cfg[i])) b->cfg[i] = default_config(p);
-            b->per_call.push_back(i);
-            b->described[i] = 1;
+            if (!b->forced[i] && !table_lookup(p, beta0, &cfg[i])) cfg[i] = default_config(p);
+            next.per_call.push_back(i);
+            described[i] = 1;
             continue;
         }
-        if (add_boxes(b, i, beta0, &boxes)) continue;
+        if (add_boxes(b, i, beta0, &next, &boxes)) continue;
         const void* Bin = q.B_in ? q.B_in : q.B;
         ttx_config used;
-        ttx_status st = batch_describe(p, b->forced[i] && b->described[i] ? &b->cfg[i] : nullptr, beta0, q.A, Bin,
-                                       q.B, q.alpha, q.beta, &desc[i], &used);
+        ttx_status st = batch_describe(p, b->forced[i] && described[i] ? &cfg[i] : nullptr, beta0, q.A, Bin, q.B,
+                                       q.alpha, q.beta, &desc[i], &used);
         if (st != TTX_OK) return st;
-        b->cfg[i] = used;
-        b->described[i] = 1;
+        cfg[i] = used;
+        described[i] = 1;
         total += desc[i].tiles;
         if (total >= (uint64_t(1) << 32)) return fail(TTX_EUNSUPPORTED, "batch has too many tiles");
-        kernel.push_back(i);
+        next.order.push_back(i);
     }
     // largest problems first, so that the chunks claimed last are short ones
-    b->order = kernel;
-    std::stable_sort(b->order.begin(), b->order.end(), [&](int x, int y) {
+    std::stable_sort(next.order.begin(), next.order.end(), [&](int x, int y) {
         return b->prob[x].elements * elem_bytes(b->prob[x].dtype) >
                b->prob[y].elements * elem_bytes(b->prob[y].dtype);
     });
-    b->nk = int(kernel.size());
-    b->desc.resize(b->nk);
-    for (int i = 0; i < b->nk; ++i) b->desc[i] = desc[b->order[i]];
-    b->chunk_prefix.assign(b->nk + 1, 0);
-    b->total = total + boxes;
-    b->chunks = b->nk ? batch_layout(b->desc.data(), b->nk, b->chunk_prefix.data(), &b->grid) : 0;
-    if (!b->nk) b->grid = 0;
-    layout_boxes(b, boxes);
+    next.nk = int(next.order.size());
+    next.desc.resize(next.nk);
+    for (int i = 0; i < next.nk; ++i) next.desc[i] = desc[next.order[i]];
+    next.chunk_prefix.assign(next.nk + 1, 0);
+    next.total = total + boxes;
+    if (next.nk) next.chunks = batch_layout(next.desc.data(), next.nk, next.chunk_prefix.data(), &next.grid);
+    layout_boxes(&next, boxes);
+    static_cast<BatchLayout&>(*b) = std::move(next);
+    b->cfg = std::move(cfg);
+    b->described = std::move(described);
     return TTX_OK;
 }
 
@@ -650,17 +655,10 @@ static hipError_t launch_per_call(const ttx_batch* b, hipStream_t stream) {
 
 static ttx_status upload(ttx_batch* b, hipStream_t stream) {
     const int count = b->nk;
-    const size_t at = box_offset(b), need = at + box_bytes(b);
-    if (b->d_work && b->work_bytes < need) {   // tuning moved problems between the two kernels
-        (void)hipFree(b->d_work);
-        b->d_work = nullptr;
-    }
-    if (!b->d_work) {
-        if (hipMalloc(reinterpret_cast<void**>(&b->d_work), need) != hipSuccess)
-            return fail(TTX_ENOMEM, "batch descriptor allocation failed");
-        b->work_bytes = need;
-        b->counter_at = size_t(-1);
-    }
+    const size_t at = box_offset(b);
+    if (!b->d_work &&
+        hipMalloc(reinterpret_cast<void**>(&b->d_work), block_bytes(int(b->prob.size()))) != hipSuccess)
+        return fail(TTX_ENOMEM, "batch descriptor allocation failed");
     if (b->counter_at != counter_offset(count)) {
         // the claim counter starts at zero; every launch leaves it at zero
         if (hipMemsetAsync(b->d_work + counter_offset(count), 0, 2 * sizeof(uint32_t), stream) != hipSuccess)
@@ -791,19 +789,24 @@ ttx_status ttx_batch_update(ttx_batch* b, int count, const ttx_problem* problems
     const uint32_t old_chunks = b->chunks;
     const int old_grid = b->grid;
     const BoxBatchGrid old_boxes = b->box_grid;
-    const size_t old_work = b->work_bytes, old_nb = b->box.size();
+    const size_t old_nb = b->box.size();
     const int old_nk = b->nk;
-    b->src.assign(problems, problems + count);
-    for (int i = 0; i < count; ++i) b->forced[i] = b->prob[i].family != TTX_FAMILY_EMPTY;
+    std::vector<ttx_problem> src(problems, problems + count);
+    std::vector<int> forced(count);
+    for (int i = 0; i < count; ++i) forced[i] = b->prob[i].family != TTX_FAMILY_EMPTY;
+    src.swap(b->src);
+    forced.swap(b->forced);
     ttx_status st = describe_all(b);
-    if (st != TTX_OK) return st;
+    if (st != TTX_OK) {
+        src.swap(b->src);
+        forced.swap(b->forced);
+        return st;
+    }
     // per-call launches carry their pointers in the graph: capture again
     if (b->chunks != old_chunks || b->grid != old_grid || !b->per_call.empty() || b->nk != old_nk ||
         b->box.size() != old_nb || std::memcmp(&b->box_grid, &old_boxes, sizeof(old_boxes)) != 0)
         drop_graph(b);
-    st = upload(b, stream);
-    if (b->work_bytes != old_work) drop_graph(b);   // a new work block
-    return st;
+    return upload(b, stream);
 }
 
 // A tuned batched configuration replaces the current one only when it is

@@ -1,0 +1,49 @@
+"""Updates of a batch against a recording HIP runtime (no GPU): whatever the
+new scalars, the launches find their tables, also where device memory has run
+out since the batch was created."""
+import pytest
+
+import fake_hip
+
+_BATCH = """
+import random
+import workloads
+def batch(seed, betas):
+    # a few uneven problems at made-up addresses; betas[i % len(betas)] each
+    r, at, out = random.Random(seed), 1 << 40, []
+    for i in range(r.choice([1, 2, 5])):
+        n = r.randint(2, 4)
+        size = [r.choice([3, 8, 17, 32, 60, 96, 200]) for _ in range(n)]
+        perm = list(range(n))
+        r.shuffle(perm)
+        es = r.choice([4, 8])
+        step = (workloads.elements(size) * es + 511) // 256 * 256
+        out.append(ttx.make_problem(ttx.F32 if es == 4 else ttx.F64, perm, size, 1.5, at, betas[i % len(betas)], at + step))
+        at += 2 * step
+    return out
+"""
+
+
+@pytest.fixture(scope="module")
+def runtime(tmp_path_factory):
+    return fake_hip.build(tmp_path_factory.mktemp("fake"))
+
+
+def test_updates_allocate_nothing_and_keep_launches_sound(runtime):
+    fake_hip.run(runtime, _BATCH + """
+launched = 0
+for seed in range(60):
+    for before, after in (([0.0], [0.5]), ([0.5], [0.0]), ([0.0, 0.5], [0.5, 0.0])):
+        fake.fake_reset()
+        b = ttx.ttx_batch_create(batch(seed, before))
+        ttx.ttx_batch_execute(b)
+        fake.fake_fail_mallocs_after(0)
+        for betas in (after, before, after):
+            ttx.ttx_batch_update(b, batch(seed, betas))
+            ttx.ttx_batch_execute(b)
+            ttx.ttx_batch_execute_direct(b)
+        ttx.ttx_batch_destroy(b)
+        launched += sum("k_box_batch" in name for name, _, _ in launches())
+        assert fake.fake_unsound() == 0, (seed, before, after)
+assert launched > 500, launched
+""")
