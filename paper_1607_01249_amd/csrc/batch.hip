@@ -19,6 +19,7 @@
 #include <algorithm>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -52,6 +53,10 @@ struct ttx_batch : BatchLayout {
     std::vector<char> described;         // cfg is filled in (problems in box tiles: when it is asked for)
     bool boxes = false;                  // untuned problems run box tiles where they have them
     std::vector<int> tuned;              // problems that keep a tuned configuration
+    // each problem's boxes by beta class (shapes don't change), chosen when
+    // first asked for; null after that: it has none
+    std::vector<std::unique_ptr<const ttx::BoxPlan>> plan[2];
+    std::vector<char> planned[2];
     unsigned char* d_work = nullptr;     // the tables on the device (see block_bytes)
     size_t counter_at = size_t(-1);      // where the claim counter was cleared
     hipStream_t cap_stream = nullptr;
@@ -531,12 +536,26 @@ static ttx_status config_of(const ttx_batch* b, int i, ttx_config* config) {
                           q.B_in ? q.B_in : q.B, q.B, q.alpha, q.beta, &d, config);
 }
 
+// Problem i's boxes, null if it has none.  A choice takes 16 us of host time,
+// so it is made once: updates of 512 problems took 9 to 13 ms with a choice
+// in each, where a launch of theirs takes 0.8 ms.
+static const BoxPlan* boxes_of(ttx_batch* b, int i, bool beta0) {
+    if (!b->planned[beta0][i]) {
+        std::unique_ptr<BoxPlan> bp(new BoxPlan);
+        if (plan_box(b->prob[i], beta0, bp.get(), true)) b->plan[beta0][i] = std::move(bp);
+        b->planned[beta0][i] = 1;
+    }
+    return b->plan[beta0][i].get();
+}
+
 // Adds problem i to the launch of boxes if it has them.
-static bool add_boxes(const ttx_batch* b, int i, bool beta0, BatchLayout* out, uint64_t* boxes) {
+static bool add_boxes(ttx_batch* b, int i, bool beta0, BatchLayout* out, uint64_t* boxes) {
     const ttx_problem& q = b->src[i];
     const Problem& p = b->prob[i];
-    BoxPlan bp;
-    if (!b->boxes || b->tuned[i] || !plan_box(p, beta0, &bp, true)) return false;
+    if (!b->boxes || b->tuned[i]) return false;
+    const BoxPlan* const plan = boxes_of(b, i, beta0);
+    if (!plan) return false;
+    const BoxPlan& bp = *plan;
     if (*boxes + bp.s.ntiles >= uint64_t(1) << 22) return false;   // workgroups of one launch, whole chunks
     *boxes += bp.s.ntiles;
     BoxBatchDesc d;
@@ -690,6 +709,11 @@ static ttx_status prepare(ttx_batch* b, int count, const ttx_problem* problems) 
     b->forced.assign(count, 0);
     b->tuned.assign(count, 0);
     b->described.assign(count, 0);
+    for (int z = 0; z < 2 && b->boxes; ++z) {
+        b->plan[z].clear();
+        b->plan[z].resize(count);
+        b->planned[z].assign(count, 0);
+    }
     for (int i = 0; i < count; ++i) {
         ttx_status st = problem_from(problems[i], &b->prob[i]);
         if (st == TTX_OK) {
@@ -958,8 +982,8 @@ ttx_status ttx_batch_tune(ttx_batch* b, int max_candidates, int reps) {
         if (nc <= 0) continue;
         ++nc;
         // and, last, the boxes that the problem runs without a tuned configuration
-        BoxPlan bp;
-        const bool boxed = b->boxes && plan_box(p, beta0, &bp, true);
+        const BoxPlan* const box = b->boxes ? boxes_of(b, int(i), beta0) : nullptr;
+        const bool boxed = box != nullptr;
         // scratch pointers keep the real pointers' offsets modulo 16 bytes, so
         // that each candidate runs the same vector variant it will run for real
         const uintptr_t offa = reinterpret_cast<uintptr_t>(q.A) & 15;
@@ -973,7 +997,7 @@ ttx_status ttx_batch_tune(ttx_batch* b, int max_candidates, int reps) {
                 const void* a = static_cast<const char*>(A) + offa;
                 void* bb = static_cast<char*>(B) + offb;
                 if (c == nc)
-                    return launch_box(p, bp, beta0, a, beta0 ? nullptr : bb, bb, Scalar(1.0), Scalar(beta0 ? 0.0 : 1.0), s);
+                    return launch_box(p, *box, beta0, a, beta0 ? nullptr : bb, bb, Scalar(1.0), Scalar(beta0 ? 0.0 : 1.0), s);
                 if (batch_describe(p, &cands[c], beta0, a, bb, bb, 1.0, beta0 ? 0.0 : 1.0, &one, nullptr) != TTX_OK)
                     return hipErrorInvalidValue;
                 uint32_t pre[2];

@@ -47,3 +47,20 @@ for seed in range(60):
         assert fake.fake_unsound() == 0, (seed, before, after)
 assert launched > 500, launched
 """)
+
+
+def test_updates_choose_no_boxes_again(runtime):
+    """A batch's shapes stay: each problem's boxes are chosen once per beta class."""
+    fake_hip.run(runtime, _BATCH + """
+for seed in range(12):
+    q = batch(seed, [0.0])
+    fake.fake_reset()
+    b = ttx.ttx_batch_create(q)
+    assert fake.fake_plans() == len(q), (fake.fake_plans(), len(q))
+    ttx.ttx_batch_update(b, batch(seed, [0.0]))
+    assert fake.fake_plans() == len(q), (fake.fake_plans(), len(q))
+    for betas in ([0.5], [0.0], [-0.25], [0.0, 0.5]):
+        ttx.ttx_batch_update(b, batch(seed, betas))
+    assert fake.fake_plans() == 2 * len(q), (fake.fake_plans(), len(q))
+    ttx.ttx_batch_destroy(b)
+""")
