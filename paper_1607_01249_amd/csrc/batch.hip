@@ -34,7 +34,6 @@ struct BatchLayout {
     std::vector<int> per_call;           // problems launched with their per-call kernels
     std::vector<ttx::BatchDesc> desc;    // kernel problems, in work order
     std::vector<uint32_t> chunk_prefix;  // over the work order
-    std::vector<int> order;              // work position -> problem index
     int nk = 0;                          // problems in the persistent kernel
     std::vector<ttx::BoxBatchDesc> box;  // problems in box tiles
     std::vector<uint32_t> box_first, box_bucket;   // first chunk per problem, first problem per stretch of chunks
@@ -536,7 +535,7 @@ static ttx_status config_of(const ttx_batch* b, int i, ttx_config* config) {
                           q.B_in ? q.B_in : q.B, q.B, q.alpha, q.beta, &d, config);
 }
 
-// Problem i's boxes, null if it has none.  A choice takes 16 us of host time,
+// Problem i's boxes, null if it has none.  A choice takes 6 us of host time,
 // so it is made once: updates of 512 problems took 9 to 13 ms with a choice
 // in each, where a launch of theirs takes 0.8 ms.
 static const BoxPlan* boxes_of(ttx_batch* b, int i, bool beta0) {
@@ -615,7 +614,9 @@ static ttx_status describe_all(ttx_batch* b) {
     BatchLayout next;
     std::vector<ttx_config> cfg = b->cfg;
     std::vector<char> described = b->described;
-    std::vector<BatchDesc> desc(count);
+    std::vector<BatchDesc> desc;     // kernel problems
+    std::vector<int> kernel, work;   // their problems, and their work order
+    if (b->boxes) next.box.reserve(count);
     uint64_t total = 0, boxes = 0;
     for (int i = 0; i < count; ++i) {
         const ttx_problem& q = b->src[i];
@@ -631,23 +632,25 @@ static ttx_status describe_all(ttx_batch* b) {
         if (add_boxes(b, i, beta0, &next, &boxes)) continue;
         const void* Bin = q.B_in ? q.B_in : q.B;
         ttx_config used;
+        desc.emplace_back();
         ttx_status st = batch_describe(p, b->forced[i] && described[i] ? &cfg[i] : nullptr, beta0, q.A, Bin, q.B,
-                                       q.alpha, q.beta, &desc[i], &used);
+                                       q.alpha, q.beta, &desc.back(), &used);
         if (st != TTX_OK) return st;
         cfg[i] = used;
         described[i] = 1;
-        total += desc[i].tiles;
+        total += desc.back().tiles;
         if (total >= (uint64_t(1) << 32)) return fail(TTX_EUNSUPPORTED, "batch has too many tiles");
-        next.order.push_back(i);
+        work.push_back(int(kernel.size()));
+        kernel.push_back(i);
     }
     // largest problems first, so that the chunks claimed last are short ones
-    std::stable_sort(next.order.begin(), next.order.end(), [&](int x, int y) {
-        return b->prob[x].elements * elem_bytes(b->prob[x].dtype) >
-               b->prob[y].elements * elem_bytes(b->prob[y].dtype);
+    std::stable_sort(work.begin(), work.end(), [&](int x, int y) {
+        const Problem &p = b->prob[kernel[x]], &q = b->prob[kernel[y]];
+        return p.elements * elem_bytes(p.dtype) > q.elements * elem_bytes(q.dtype);
     });
-    next.nk = int(next.order.size());
-    next.desc.resize(next.nk);
-    for (int i = 0; i < next.nk; ++i) next.desc[i] = desc[next.order[i]];
+    next.nk = int(kernel.size());
+    next.desc.reserve(next.nk);
+    for (int k : work) next.desc.push_back(desc[k]);
     next.chunk_prefix.assign(next.nk + 1, 0);
     next.total = total + boxes;
     if (next.nk) next.chunks = batch_layout(next.desc.data(), next.nk, next.chunk_prefix.data(), &next.grid);

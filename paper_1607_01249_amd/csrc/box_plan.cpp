@@ -1,6 +1,6 @@
 // Choice of a box tile (host only; see box.h).  Every pair of candidate runs
 // gives a box, small ones also filled up by a third index; the cheapest by an
-// estimate of its time is taken (40 to 60 us of host time for a new problem).
+// estimate of its time is taken (4 to 6 us of host time, up to 30).
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -12,6 +12,11 @@ namespace ttx {
 namespace {
 
 constexpr int kBoxBytes = 16384;
+
+// a / b and its ceiling for the sizes here (extents of tensors below 4 GiB):
+// divisions of 64 bits took a third of a choice's time.
+int64_t quotient(int64_t a, int64_t b) { return uint32_t(a) / uint32_t(b); }
+int64_t ceiling(int64_t a, int64_t b) { return quotient(a + b - 1, b); }
 
 // One side's run: its first `whole` indices and `t` steps of the next one.
 struct Run {
@@ -37,10 +42,9 @@ int runs_of(const Problem& p, const int* order, bool in_a, int es, Run* out, int
         const Dim& d = p.dim[order[k]];
         int64_t last = 0;
         for (int64_t want = 64; want <= 4096 && n < cap; want *= 2) {
-            int64_t t = std::max<int64_t>(1, want / es / len);
+            int64_t t = std::max<int64_t>(1, quotient(quotient(want, es), len));
             if (t >= d.size || len * t > most) break;
-            const int64_t pieces = (d.size + t - 1) / t;
-            if (len != 1 || t % line || d.size < 4 * t) t = (d.size + pieces - 1) / pieces;
+            if (len != 1 || t & (line - 1) || d.size < 4 * t) t = ceiling(d.size, ceiling(d.size, t));
             if (t == last || t >= d.size) continue;
             last = t;
             out[n++] = Run{k, t, len * t};
@@ -55,26 +59,30 @@ int runs_of(const Problem& p, const int* order, bool in_a, int es, Run* out, int
 
 // One box: its extents t (by index), the runs they give and what they cost.
 struct Box {
-    int64_t t[kMaxDims];
-    int64_t volume, LA, LB;      // elements of the box and of its runs
+    int t[kMaxDims];
+    int volume, LA, LB;          // elements of the box and of its runs
     int sa, sb, sc;              // indices that the runs cut, and a third one that the box cuts, -1: none
     int in_run_a, in_run_b;      // positions (A's order, B's order) that a run holds
-    int64_t nua, nub;            // units of a full box
+    int nua, nub;                // units of a full box
     double tiles;
 };
+
+// Boxes along index d; most indices need no division.
+int64_t steps_of(const Problem& p, const Box& b, int d) {
+    const int64_t size = p.dim[d].size, t = b.t[d];
+    return t == 1 ? size : t == size ? 1 : ceiling(size, t);
+}
 
 // Fills in a box from its extents; false where the kernel can't take it.
 bool box_of(const Problem& p, Box* b) {
     const int ea = elem_bytes(p.dtype_a), eb = elem_bytes(p.dtype);
     const int UA = 16 / ea, UB = 16 / eb;
-    const int64_t* t = b->t;
+    const int* t = b->t;
     int dims = 0;
     b->volume = 1;
-    b->tiles = 1;
     for (int d = 0; d < p.n; ++d) {
         b->volume *= t[d];
         dims += t[d] > 1;
-        b->tiles *= double((p.dim[d].size + t[d] - 1) / t[d]);
     }
     if (dims > kBoxDims || b->volume * eb > kBoxBytes || b->volume * ea > 2 * kBoxBytes) return false;
     // a run: whole indices that follow each other in memory, and part of the next
@@ -108,10 +116,14 @@ bool box_of(const Problem& p, Box* b) {
             if (b->sc >= 0) return false;
             b->sc = d;
         }
-    b->nua = b->volume / b->LA * ((b->LA + UA - 1) / UA);
-    b->nub = b->volume / b->LB * ((b->LB + UB - 1) / UB);
+    const int runs_a = b->volume / b->LA, runs_b = b->volume / b->LB;
+    b->nua = runs_a * ((b->LA + UA - 1) / UA);
+    b->nub = runs_b * ((b->LB + UB - 1) / UB);
     if (b->nua > kThreads * kBoxUnits || b->nub > kThreads * kBoxUnits) return false;
-    return b->volume / b->LA * (b->LA + 1) + UA <= box_lds(eb, kBoxUnits);   // with an odd pitch
+    if (runs_a * (b->LA + 1) + UA > box_lds(eb, kBoxUnits)) return false;   // with an odd pitch
+    b->tiles = 1;
+    for (int d = 0; d < p.n; ++d) b->tiles *= double(steps_of(p, *b, d));
+    return true;
 }
 
 // Whether two units per thread hold the box.
@@ -142,8 +154,8 @@ double box_cost(const Problem& p, bool beta0, const Box& b) {
     const double n = double(p.elements), sides = beta0 ? 1.0 : 2.0;   // accesses of B
     // boxes between one box and the one that goes on with its run of A or B
     double da = 1.0, db = 1.0;
-    for (int k = 0, d; k < p.n && (d = p.perm[k]) != b.sa; ++k) da *= double((p.dim[d].size + b.t[d] - 1) / b.t[d]);
-    for (int k = 0, d; k < p.n && (d = p.perm[k]) != b.sb; ++k) db *= double((p.dim[d].size + b.t[d] - 1) / b.t[d]);
+    for (int k = 0, d; b.sa >= 0 && (d = p.perm[k]) != b.sa; ++k) da *= double(steps_of(p, b, d));
+    for (int k = 0, d; b.sb >= 0 && (d = p.perm[k]) != b.sb; ++k) db *= double(steps_of(p, b, d));
     bool lines_a = b.LA * ea % 128 == 0;
     const bool lines_b = whole_lines_b(p, b);
     for (int k = b.in_run_a; k < p.n; ++k) lines_a = lines_a && p.dim[k].sa * ea % 128 == 0;
@@ -167,55 +179,80 @@ void each_box(const Problem& p, F&& f) {
         for (int j = 0; j < nb; ++j) {
             Box b;
             for (int d = 0; d < p.n; ++d) b.t[d] = 1;
-            for (int k = 0; k < ra[i].whole; ++k) b.t[k] = p.dim[k].size;
-            if (ra[i].t) b.t[ra[i].whole] = ra[i].t;
-            for (int k = 0; k < rb[j].whole; ++k) b.t[p.perm[k]] = p.dim[p.perm[k]].size;
-            if (rb[j].t) b.t[p.perm[rb[j].whole]] = std::max(b.t[p.perm[rb[j].whole]], rb[j].t);
+            for (int k = 0; k < ra[i].whole; ++k) b.t[k] = int(p.dim[k].size);
+            if (ra[i].t) b.t[ra[i].whole] = int(ra[i].t);
+            for (int k = 0; k < rb[j].whole; ++k) b.t[p.perm[k]] = int(p.dim[p.perm[k]].size);
+            if (rb[j].t) b.t[p.perm[rb[j].whole]] = std::max(b.t[p.perm[rb[j].whole]], int(rb[j].t));
             if (!box_of(p, &b)) continue;
             f(b);
-            // a small box filled up to two or four units a thread, with the
-            // next indices of A's order or of B's
-            for (int side = 0; side < 2 && std::max(b.nua, b.nub) <= kThreads; ++side)
-                for (int64_t most = 2 * kThreads; most <= 4 * kThreads; most *= 2) {
-                    Box c = b;
-                    for (int k = 0; k < p.n; ++k) {
+            // a small box filled up to two, then four units a thread, with the
+            // next indices of A's order or of B's: whole ones, then part of one
+            for (int side = 0; side < 2 && std::max(b.nua, b.nub) <= kThreads; ++side) {
+                Box c = b, e;
+                int k = 0;
+                for (int most = 2 * kThreads; most <= 4 * kThreads && k < p.n; most *= 2) {
+                    bool cut = false;   // e ends with part of index k: the next pass goes on there
+                    for (; k < p.n; ++k) {
                         const int d = side ? p.perm[k] : k;
-                        const int64_t room = most / std::max(c.nua, c.nub), size = p.dim[d].size;
                         if (c.t[d] > 1 || d == c.sa || d == c.sb) continue;
+                        const int64_t room = quotient(most, std::max(c.nua, c.nub)), size = p.dim[d].size;
                         if (room < 2) break;
-                        Box e = c;
-                        const int64_t pieces = (size + room - 1) / room;
-                        e.t[d] = (size + pieces - 1) / pieces;
-                        if (!box_of(p, &e)) break;
-                        c = e;
-                        if (pieces > 1) break;
+                        const int64_t pieces = ceiling(size, room);
+                        e = c;
+                        e.t[d] = int(ceiling(size, pieces));
+                        const bool fits = box_of(p, &e);
+                        if (pieces > 1) {
+                            cut = fits;
+                            break;
+                        }
+                        if (!fits) k = p.n;
+                        else c = e;
                     }
-                    if (c.volume > b.volume) f(c);
+                    if (cut) f(e);
+                    else if (c.volume > b.volume) f(c);
                 }
+            }
         }
 }
 
-// LDS cycles of half a wavefront's first units (put and gather) in a full box:
-// a bank serves one word a cycle, 32 words in all.  `least`: without conflicts.
+// Where half a wavefront's first units of a full box lie in LDS, element by
+// element (those that are put, then those that are gathered): the run of A
+// and the place in it.  Layouts differ in the distance between runs and in the
+// skew only, so the kernel's offsets are taken once, with runs a power of two
+// apart.
+constexpr int kLanes = 32;
+struct BankLanes {
+    int n;                           // elements of a lane
+    int run[8][kLanes], in[8][kLanes];
+};
 template <int UA, int UB>
-int bank_cycles(const BoxShape& s, int elem, int* least) {
-    constexpr int kLanes = 32;
-    const int words = elem / 4, group = 32 / words;   // lanes served together
+void bank_lanes(const BoxShape& s, int log, BankLanes* out) {
     const BoxCoord c{0, 0, s.tA, s.tB, s.tC};
-    int at[UA + UB][kLanes];
+    out->n = UA + UB;
     for (int lane = 0; lane < kLanes; ++lane) {
         BoxUnits<UA, UB, 1> u;
         u.init(s, lane, c);
-        for (int j = 0; j < UA; ++j) at[j][lane] = u.put(0, j) + (u.put(0, j) >> s.skew);
-        for (int j = 0; j < UB; ++j) at[UA + j][lane] = u.gather(0, j);
+        for (int j = 0; j < UA + UB; ++j) {
+            const int l = j < UA ? u.put(0, j) : u.gather(0, j - UA);
+            out->run[j][lane] = l >> log;
+            out->in[j][lane] = l & ((1 << log) - 1);
+        }
     }
-    const int from = s.aligned ? UA : 0, units = s.aligned ? kLanes / 8 : 0;   // whole units: 8 lanes a cycle
-    int cycles = units;
-    for (int j = from; j < UA + UB; ++j)
+}
+
+// LDS cycles of these accesses: a bank serves one word a cycle, 32 words in
+// all.  `aligned`: the first `put` elements go as whole units, 8 lanes a cycle.
+// Counts up to `limit`.
+int bank_cycles(const BankLanes& lanes, int pitch, int skew, bool aligned, int put, int elem, int limit) {
+    const int words = elem / 4, group = 32 / words;   // lanes served together
+    int cycles = aligned ? kLanes / 8 : 0;
+    for (int j = aligned ? put : 0; j < lanes.n && cycles < limit; ++j)
         for (int g = 0; g < kLanes; g += group) {
             int seen[32][32], n[32] = {}, most = 1;
             for (int lane = g; lane < g + group; ++lane) {
-                const int l = at[j][lane], bank = l * words % 32;
+                int l = lanes.run[j][lane] * pitch + lanes.in[j][lane];
+                l += l >> skew;
+                const int bank = l * words % 32;
                 bool again = false;   // the same element: one access
                 for (int k = 0; k < n[bank]; ++k) again |= seen[bank][k] == l;
                 if (!again) seen[bank][n[bank]++] = l;
@@ -223,62 +260,66 @@ int bank_cycles(const BoxShape& s, int elem, int* least) {
             }
             cycles += most;
         }
-    *least = units + (UA + UB - from) * (kLanes / group);
     return cycles;
-}
-
-int bank_cycles(const Problem& p, const BoxShape& s, int* least) {
-    const int ea = elem_bytes(p.dtype_a), eb = elem_bytes(p.dtype);
-    if (ea == eb)
-        return eb == 4   ? bank_cycles<4, 4>(s, 4, least)
-               : eb == 8 ? bank_cycles<2, 2>(s, 8, least)
-                         : bank_cycles<1, 1>(s, 16, least);
-    if (ea < eb) return eb == 8 ? bank_cycles<4, 2>(s, 8, least) : bank_cycles<2, 1>(s, 16, least);
-    return eb == 4 ? bank_cycles<2, 4>(s, 4, least) : bank_cycles<1, 2>(s, 8, least);
 }
 
 // The LDS layout: A's runs one after the other, with the distance between them
 // (whole units, or an odd number of elements) and the skew that cost the
 // fewest cycles; false if none fits into `cap` elements.
 bool place(const Problem& p, const Box& b, int cap, BoxShape* s) {
-    const int UA = 16 / elem_bytes(p.dtype_a), eb = elem_bytes(p.dtype);
+    const int ea = elem_bytes(p.dtype_a), eb = elem_bytes(p.dtype), UA = 16 / ea, UB = 16 / eb;
     const int shift = eb == 4 ? 5 : eb == 8 ? 4 : 3;
-    int best = 1 << 30;
-    BoxShape chosen = *s;
-    for (int option = 0; option < 4; ++option) {
-        const bool units = option == 0;
-        if (units && b.LA % UA) continue;
-        const int64_t odd = units ? UA : 1;
-        const int64_t pitch = option == 2 ? b.LA : (b.LA / odd) % 2 ? b.LA : b.LA + odd;
-        s->aligned = units && elem_bytes(p.dtype_a) == eb;
-        s->skew = option < 2 ? 31 : shift;
-        int64_t ls[kMaxDims], at = 1;
+    auto lay_out = [&](int pitch) {
+        int ls[kMaxDims], at = 1;
         for (int d = 0; d < p.n; ++d) {
             if (d == b.in_run_a) at = pitch;
             ls[d] = at;
             at *= b.t[d];
         }
         for (int k = 0, d = 0; d < p.n; ++d)
-            if (b.t[d] > 1 || d == b.sa || d == b.sb) s->dA[k++].ls = int(ls[d]);
+            if (b.t[d] > 1 || d == b.sa || d == b.sb) s->dA[k++].ls = ls[d];
         for (int k = 0, q = 0; q < p.n; ++q) {
             const int d = p.perm[q];
-            if (b.t[d] > 1 || d == b.sa || d == b.sb) s->dB[k++].ls = int(ls[d]);
+            if (b.t[d] > 1 || d == b.sa || d == b.sb) s->dB[k++].ls = ls[d];
         }
-        const int64_t last = b.volume / b.LA * pitch + UA;
-        if (last + (last >> s->skew) > cap) continue;
-        int least = 0;
-        const int cycles = bank_cycles(p, *s, &least);
-        const int total = cycles + (option < 2 ? 0 : 12);   // a skew costs instructions too
-        if (total < best) best = total, chosen = *s;
-        if (cycles == least) break;   // what follows is no better
+    };
+    int log = 0;
+    while ((1 << log) < b.LA) ++log;
+    lay_out(1 << log);
+    s->skew = 31;
+    BankLanes lanes;
+    if (ea == eb)
+        eb == 4 ? bank_lanes<4, 4>(*s, log, &lanes) : eb == 8 ? bank_lanes<2, 2>(*s, log, &lanes) : bank_lanes<1, 1>(*s, log, &lanes);
+    else if (ea < eb)
+        eb == 8 ? bank_lanes<4, 2>(*s, log, &lanes) : bank_lanes<2, 1>(*s, log, &lanes);
+    else
+        eb == 4 ? bank_lanes<2, 4>(*s, log, &lanes) : bank_lanes<1, 2>(*s, log, &lanes);
+    const int fewest = (UA + UB) * eb / 4;   // single elements without conflicts
+    int best = 1 << 30, chosen = 0;
+    for (int option = 0; option < 4; ++option) {
+        const bool units = option == 0;
+        const int extra = option < 2 ? 0 : 12;   // a skew costs instructions too
+        if (units && b.LA % UA) continue;
+        if (best <= fewest + extra) break;       // what follows is no better
+        const int odd = units ? UA : 1;
+        const int pitch = option == 2 ? b.LA : (b.LA / odd) % 2 ? b.LA : b.LA + odd;
+        const int skew = option < 2 ? 31 : shift, last = b.volume / b.LA * pitch + UA;
+        if (last + (last >> skew) > cap) continue;
+        const bool aligned = units && ea == eb;
+        const int cycles = bank_cycles(lanes, pitch, skew, aligned, UA, eb, best - extra) + extra;
+        if (cycles >= best) continue;
+        best = cycles;
+        chosen = pitch;
+        s->aligned = aligned;
+        s->skew = skew;
     }
-    *s = chosen;
+    lay_out(chosen);
     return best < (1 << 30);
 }
 
 bool make_box(const Problem& p, bool beta0, const Box& b, BoxPlan* out) {
     const int UA = 16 / elem_bytes(p.dtype_a);
-    const int64_t* t = b.t;
+    const int* t = b.t;
     const int64_t LA = b.LA, LB = b.LB;
     const int sa = b.sa, sb = b.sb, in_run_a = b.in_run_a, in_run_b = b.in_run_b;
     BoxShape& s = out->s;
@@ -321,7 +362,7 @@ bool make_box(const Problem& p, bool beta0, const Box& b, BoxPlan* out) {
         const int d = p.perm[k];
         if (t[d] == p.dim[d].size) continue;
         if (s.ng == kBoxSteps) return false;
-        const uint64_t cnt = uint64_t((p.dim[d].size + t[d] - 1) / t[d]);
+        const uint64_t cnt = uint64_t(steps_of(p, b, d));
         tiles *= cnt;
         if (tiles >= (uint64_t(1) << 23)) return false;   // workgroups of one launch
         BoxStep& g = s.g[s.ng++];

@@ -64,3 +64,33 @@ for seed in range(12):
     assert fake.fake_plans() == 2 * len(q), (fake.fake_plans(), len(q))
     ttx.ttx_batch_destroy(b)
 """)
+
+
+def test_creation_costs_what_planning_costs(runtime):
+    """The choice of boxes for 512 uneven problems takes about the host time of
+    the heuristic configurations that it stands in for (ttx_batch_plan): best
+    of 15 rounds each, in turn."""
+    fake_hip.run(runtime, """
+import ctypes, time
+import workloads
+from paper_1607_01249_amd import _ttx
+at, problems = 1 << 40, []
+for p in workloads.batched_problems():
+    step = (workloads.elements(p["size"]) * p["dtype"].itemsize + 511) // 256 * 256
+    problems.append(ttx.make_problem(ttx.F32 if p["dtype"].itemsize == 4 else ttx.F64, p["perm"], p["size"], p["alpha"],
+                                     at, p["beta"], at + step))
+    at += 2 * step
+array, n, L = _ttx._problem_array(problems), len(problems), ttx.lib()
+configs, tiles, batch = (ttx.Config * n)(), (ctypes.c_int64 * n)(), ctypes.c_void_p()
+create = plan = 1e9
+for _ in range(15):
+    t0 = time.process_time()
+    assert L.ttx_batch_create(ctypes.byref(batch), n, array) == 0
+    t1 = time.process_time()
+    assert L.ttx_batch_plan(n, array, configs, tiles) == 0
+    t2 = time.process_time()
+    L.ttx_batch_destroy(batch)
+    create, plan = min(create, t1 - t0), min(plan, t2 - t1)
+print("create %.2f ms, plan %.2f ms, %.2f" % (create * 1e3, plan * 1e3, create / plan))
+assert create < 1.6 * plan, (create, plan)
+""")
