@@ -36,6 +36,7 @@ struct BatchLayout {
     std::vector<uint32_t> chunk_prefix;  // over the work order
     int nk = 0;                          // problems in the persistent kernel
     std::vector<ttx::BoxBatchDesc> box;  // problems in box tiles
+    std::vector<char> boxed;             // whether a problem is one of them
     std::vector<uint32_t> box_first, box_bucket;   // first chunk per problem, first problem per stretch of chunks
     ttx::BoxBatchGrid box_grid{};
     uint64_t total = 0;                  // tiles
@@ -616,6 +617,7 @@ static ttx_status describe_all(ttx_batch* b) {
     std::vector<char> described = b->described;
     std::vector<BatchDesc> desc;     // kernel problems
     std::vector<int> kernel, work;   // their problems, and their work order
+    next.boxed.assign(count, 0);
     if (b->boxes) next.box.reserve(count);
     uint64_t total = 0, boxes = 0;
     for (int i = 0; i < count; ++i) {
@@ -629,7 +631,8 @@ static ttx_status describe_all(ttx_batch* b) {
             described[i] = 1;
             continue;
         }
-        if (add_boxes(b, i, beta0, &next, &boxes)) continue;
+        next.boxed[i] = add_boxes(b, i, beta0, &next, &boxes);
+        if (next.boxed[i]) continue;
         const void* Bin = q.B_in ? q.B_in : q.B;
         ttx_config used;
         desc.emplace_back();
@@ -972,21 +975,24 @@ ttx_status ttx_batch_tune(ttx_batch* b, int max_candidates, int reps) {
             std::lock_guard<std::mutex> lock(g_btab_mu);
             auto it = g_btab.find(key);
             if (it != g_btab.end()) {
-                changed = changed || std::memcmp(&b->cfg[i], &it->second, sizeof(ttx_config)) != 0;
+                changed = changed || b->boxed[i] || std::memcmp(&b->cfg[i], &it->second, sizeof(ttx_config)) != 0;
                 b->cfg[i] = it->second;
                 b->forced[i] = b->tuned[i] = 1;
                 continue;
             }
         }
-        // candidate 0: the configuration the batch runs now (the heuristic
-        // choice), then the ranked batched-menu candidates
+        // candidate 0: the problem's configuration (the heuristic choice, or an
+        // earlier one), then the ranked batched-menu candidates
         cands[0] = b->cfg[i];
         int nc = batch_candidates(p, max_candidates, cands.data() + 1, int(cands.size()) - 1);
         if (nc <= 0) continue;
         ++nc;
-        // and, last, the boxes that the problem runs without a tuned configuration
-        const BoxPlan* const box = b->boxes ? boxes_of(b, int(i), beta0) : nullptr;
-        const bool boxed = box != nullptr;
+        // and, last, the boxes that the problem runs now, if it does: with plain
+        // stores, as in the launch over many problems
+        const bool boxed = b->boxed[i];
+        BoxPlan box{};
+        if (boxed) box = *boxes_of(b, int(i), beta0);
+        box.nt = false;
         // scratch pointers keep the real pointers' offsets modulo 16 bytes, so
         // that each candidate runs the same vector variant it will run for real
         const uintptr_t offa = reinterpret_cast<uintptr_t>(q.A) & 15;
@@ -1000,7 +1006,7 @@ ttx_status ttx_batch_tune(ttx_batch* b, int max_candidates, int reps) {
                 const void* a = static_cast<const char*>(A) + offa;
                 void* bb = static_cast<char*>(B) + offb;
                 if (c == nc)
-                    return launch_box(p, *box, beta0, a, beta0 ? nullptr : bb, bb, Scalar(1.0), Scalar(beta0 ? 0.0 : 1.0), s);
+                    return launch_box(p, box, beta0, a, beta0 ? nullptr : bb, bb, Scalar(1.0), Scalar(beta0 ? 0.0 : 1.0), s);
                 if (batch_describe(p, &cands[c], beta0, a, bb, bb, 1.0, beta0 ? 0.0 : 1.0, &one, nullptr) != TTX_OK)
                     return hipErrorInvalidValue;
                 uint32_t pre[2];
@@ -1013,11 +1019,11 @@ ttx_status ttx_batch_tune(ttx_batch* b, int max_candidates, int reps) {
                 return launch_batch(d_one, d_pre, 1, chunks, grid, d_cnt, s);
             },
             &best_i, &best_us, us.data());
-        // another configuration only when it is clearly faster than the
-        // current one (timing one problem alone ranks close candidates
+        // another configuration only when it is clearly faster than what the
+        // problem runs now (timing one problem alone ranks close candidates
         // differently from the full batch)
-        const double now_us = boxed ? us[nc] : us[0];
-        if (result == TTX_OK && best_i > 0 && best_i < nc && best_us < now_us * (1.0 - kBatchTuneMargin)) {
+        const int now = boxed ? nc : 0;
+        if (result == TTX_OK && best_i != now && best_us < us[now] * (1.0 - kBatchTuneMargin)) {
             b->cfg[i] = cands[best_i];
             b->forced[i] = b->tuned[i] = 1;
             changed = true;
