@@ -130,7 +130,7 @@ static ttx_status execute(const ttx_plan* plan, const Scalar& alpha, const void*
     if (st != TTX_OK) return st;
     const std::shared_ptr<const PlanExec> x = plan->load(beta0 ? 1 : 0);
     if (x->jit && x->box) {
-        if (jit_on_device(*x->jit) && box_takes(*x->box, Bout)) {
+        if (jit_on_device(*x->jit)) {
             const hipError_t e = jit_box_launch(*x->jit, p, *x->box, A, beta0 ? nullptr : Bin, Bout, alpha, beta, stream);
             if (e != hipSuccess) return fail(TTX_EHIP, std::string("kernel launch: ") + hipGetErrorString(e));
             return TTX_OK;
@@ -451,7 +451,7 @@ ttx_status ttx_plan_kernel_name(const ttx_plan* plan, double beta, const void* A
     const std::shared_ptr<const PlanExec> x = plan->load(beta0 ? 1 : 0);
     std::string name;
     TiledLaunch L;
-    if (x->jit && x->box && jit_on_device(*x->jit) && box_takes(*x->box, B))
+    if (x->jit && x->box && jit_on_device(*x->jit))
         name = jit_name(*x->jit);
     else if (x->jit && !x->box &&
              prepare_tiled(p, x->cfg, beta0, A, B, const_cast<void*>(B), Scalar(1.0), Scalar(beta), &L) &&

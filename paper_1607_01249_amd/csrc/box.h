@@ -24,6 +24,10 @@ constexpr int kBoxDims = 6;     // indices of extent > 1 in a box
 constexpr int kBoxSteps = 8;    // indices of the grid of boxes
 constexpr int kBoxUnits = 4;    // most units per thread and side
 
+// Whether B starts on a 128-byte line.  Nontemporal stores of partial lines
+// are slow, and a B that does not has them throughout.
+__host__ __device__ __forceinline__ bool box_on_line(const void* B) { return (unsigned long long)(B) % 128 == 0; }
+
 struct BoxDim {
     int ext;         // extent in the box
     int split;       // 1: split A, 2: split B, 3: both, 4: fill
@@ -242,11 +246,6 @@ struct BoxPlan {
     int units;           // per thread and side that hold the box: 2 or 4
     bool nt;             // nontemporal stores, if B starts on a line
 };
-// Whether the box's store kind suits B: nontemporal stores of partial lines
-// are slow, and a B that does not start on a line has them throughout.
-inline bool box_takes(const BoxPlan& bp, const void* B) {
-    return !bp.nt || reinterpret_cast<uintptr_t>(B) % 128 == 0;
-}
 // The best box for a problem, false if it has none (no contiguous runs of a
 // unit on both sides, offsets beyond 32 bits, empty problems).  `batched`: for
 // a launch over many problems (two units a thread, and flat problems too,

@@ -193,9 +193,11 @@ std::string jit_box_source(const Problem& p, const BoxPlan& bp, bool beta0) {
     s += "extern \"C\" __global__ __launch_bounds__(" + std::to_string(kThreads) + ", 5)\nvoid ";
     s += box_entry_name(p, bp, beta0) + "(ttx::BoxPtrs<" + T + ", " + S + "> a) {\n";
     s += "    __shared__ __align__(16) " + T + " lds[ttx::box_lds(sizeof(" + T + "), " + std::to_string(bp.units) + ")];\n";
-    s += "    ttx::box_body<" + T + ", " + S + (beta0 ? ", true, " : ", false, ") + std::to_string(bp.units);
-    s += bp.nt ? ", true" : ", false";
-    s += ">(lds, kHost, a, ttx::box_id(blockIdx.x, kHost.ntiles, kHost.chunk));\n}\n";
+    s += "    const unsigned box = ttx::box_id(blockIdx.x, kHost.ntiles, kHost.chunk);\n";
+    const std::string body = "ttx::box_body<" + T + ", " + S + (beta0 ? ", true, " : ", false, ") + std::to_string(bp.units);
+    // nontemporal stores need a B that starts on a line; the kernel takes any
+    if (bp.nt) s += "    if (ttx::box_on_line(a.Bdst)) return " + body + ", true>(lds, kHost, a, box);\n";
+    s += "    " + body + ", false>(lds, kHost, a, box);\n}\n";
     return s;
 }
 

@@ -12,7 +12,7 @@ static hipError_t launch_box_as(const BoxPlan& bp, bool beta0, const void* A, co
     static_cast<BoxPtrs<T, S>&>(a) = {static_cast<const S*>(A), static_cast<const T*>(Bsrc), static_cast<T*>(Bdst),
                                       scalar_as<T>(alpha), scalar_as<T>(beta)};
     const dim3 g(a.ntiles), b(kThreads);
-    const auto kernel = bp.nt && box_takes(bp, Bdst) ? (bp.units == 2 ? k_box<T, S, true, 2, true> : k_box<T, S, true, 4, true>)
+    const auto kernel = bp.nt && box_on_line(Bdst) ? (bp.units == 2 ? k_box<T, S, true, 2, true> : k_box<T, S, true, 4, true>)
                         : bp.units == 2 ? (beta0 ? k_box<T, S, true, 2, false> : k_box<T, S, false, 2, false>)
                                         : (beta0 ? k_box<T, S, true, 4, false> : k_box<T, S, false, 4, false>);
     hipLaunchKernelGGL(kernel, g, b, 0, stream, a);
