@@ -143,38 +143,4 @@ __global__ __launch_bounds__(kThreads, 5) void k_box(BoxArgs<T, S> a) {
     box_body<T, S, BETA0, NU, NT>(lds, a, a, box_id(blockIdx.x, a.ntiles, a.chunk));
 }
 
-// The boxes of many problems in one launch.  Every problem has whole chunks of
-// 2^chunk boxes; consecutive chunks go round the XCDs, a chunk's boxes stay on
-// one.  A table of at most kBoxBuckets entries narrows the search for a
-// chunk's problem down to those that start in one stretch of chunks (one
-// problem as a rule).  Two units a thread: the four bodies need no more
-// registers than 8 wavefronts a SIMD leave.
-__global__ __launch_bounds__(kThreads, 8) inline void k_box_batch(const BoxBatchDesc* __restrict__ desc,
-                                                                  const uint32_t* __restrict__ first,
-                                                                  const uint32_t* __restrict__ bucket, int shift,
-                                                                  int chunk, uint32_t chunks) {
-    __shared__ __align__(16) unsigned char lds[box_lds(1, 2)];
-    const uint32_t set = blockIdx.x >> (chunk + 3), r = blockIdx.x & ((8u << chunk) - 1);
-    const uint32_t c = set * 8 + (r & 7);
-    if (c >= chunks) return;
-    uint32_t lo = bucket[c >> shift], hi = bucket[(c >> shift) + 1];
-    while (lo < hi) {   // the last problem whose first chunk is c or before
-        const uint32_t mid = (lo + hi + 1) >> 1;
-        if (first[mid] <= c) lo = mid;
-        else hi = mid - 1;
-    }
-    // read through the constant address space: fields live in scalar registers
-    typedef __attribute__((address_space(4))) const BoxBatchDesc ConstDesc;
-    const BoxBatchDesc& d = *(const BoxBatchDesc*)((ConstDesc*)(desc + lo));
-    const uint32_t t = ((c - first[lo]) << chunk) + (r >> 3);
-    touch(d);
-    if (t >= d.f64.ntiles) return;   // the last chunk's tail (both kinds start with BoxShape)
-    switch (d.kind) {
-        case 0: return box_body<float, float, false, 2>(reinterpret_cast<float*>(lds), d.f32, d.f32, t);
-        case 1: return box_body<float, float, true, 2>(reinterpret_cast<float*>(lds), d.f32, d.f32, t);
-        case 2: return box_body<double, double, false, 2>(reinterpret_cast<double*>(lds), d.f64, d.f64, t);
-        default: return box_body<double, double, true, 2>(reinterpret_cast<double*>(lds), d.f64, d.f64, t);
-    }
-}
-
 }  // namespace ttx

@@ -233,6 +233,20 @@ hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) {
     *v = 256;
     return hipSuccess;
 }
+hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600* p, int) {
+    std::memset(p, 0, sizeof(*p));
+    std::strcpy(p->gcnArchName, "gfx950:sramecc+:xnack-");
+    return hipSuccess;
+}
+hipError_t hipModuleLoadData(hipModule_t* m, const void*) {
+    *m = reinterpret_cast<hipModule_t>(uintptr_t(64));
+    return hipSuccess;
+}
+hipError_t hipModuleUnload(hipModule_t) { return hipSuccess; }
+hipError_t hipModuleGetFunction(hipFunction_t* f, hipModule_t, const char*) {
+    *f = reinterpret_cast<hipFunction_t>(uintptr_t(64));
+    return hipSuccess;
+}
 hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) {
     *n = 4;
     return hipSuccess;
