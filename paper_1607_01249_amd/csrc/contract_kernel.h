@@ -213,7 +213,7 @@ struct ContractOut {
 
     __device__ __forceinline__ static int row(int lane) { return VEC ? 4 * (lane >> 4) : (lane & 15); }
     __device__ __forceinline__ static int col(int lane) { return VEC ? (lane & 15) : 4 * (lane >> 4); }
-    // rows: offsets of the wave's rows, cols: of the tile's columns from block j0 on
+    // rows: offsets of the wave's rows, cols: of the tile's columns
     __device__ __forceinline__ void init(T* c, const int64_t* rows, const int64_t* cols) {
         const int lane = threadIdx.x & 63;
         c0 = reinterpret_cast<char*>(c);
@@ -239,8 +239,8 @@ struct ContractOut {
             }
     }
     // alpha * sum, and with UPDATE + beta * what load() read
-    template <bool UPDATE, int NBA>
-    __device__ __forceinline__ void store(const Acc (&acc)[MB][NBA], int j0, T alpha, T beta) const {
+    template <bool UPDATE>
+    __device__ __forceinline__ void store(const Acc (&acc)[MB][NB], T alpha, T beta) const {
 #pragma unroll
         for (int j = 0; j < NB; ++j)
 #pragma unroll
@@ -250,14 +250,14 @@ struct ContractOut {
                     T* p = reinterpret_cast<T*>(c0 + ro[i] + co[j][g]);
                     const bool ok = ro[i] >= 0 && co[j][g] >= 0;
                     if constexpr (VEC) {
-                        Acc out = alpha * acc[i][j0 + j];
+                        Acc out = alpha * acc[i][j];
                         if constexpr (UPDATE) {
                             const Acc pb = beta * old[i][j];
                             out = out + pb;
                         }
                         if (ok) store_rows<T>(p, out);
                     } else {
-                        T out = alpha * acc[i][j0 + j][g];
+                        T out = alpha * acc[i][j][g];
                         if constexpr (UPDATE) {
                             const T pb = beta * old[i][j][g];
                             out = out + pb;
@@ -416,19 +416,14 @@ __global__ __launch_bounds__(256) void k_contract(ContractArgs a, const T* __res
             }
         return;
     }
-    // C's loads are all in flight before the first use, half a tile at a time
-    // where a whole one would take over 64 registers
-    constexpr int JB = NB * MB * 4 * int(sizeof(T)) > 256 ? NB / 2 : NB;
-#pragma unroll
-    for (int j0 = 0; j0 < NB; j0 += JB) {
-        ContractOut<T, MB, JB, VEC> out;
-        out.init(C, row_c + wave * 16 * MB, col_c + 16 * j0);
-        if (beta0) {
-            out.template store<false>(acc, j0, alpha, beta);
-        } else {
-            out.load();
-            out.template store<true>(acc, j0, alpha, beta);
-        }
+    // C's loads are all in flight before the first use (up to 64 registers)
+    Out to;
+    to.init(C, row_c + wave * 16 * MB, col_c);
+    if (beta0) {
+        to.template store<false>(acc, alpha, beta);
+    } else {
+        to.load();
+        to.template store<true>(acc, alpha, beta);
     }
 }
 
@@ -657,7 +652,7 @@ __global__ __launch_bounds__(256) void k_contract_short(ContractArgs a, const T*
         __syncthreads();
         out.template store<UPDATE>(lds, alpha, beta);
     } else {
-        out.template store<UPDATE>(acc, 0, alpha, beta);
+        out.template store<UPDATE>(acc, alpha, beta);
     }
 }
 
