@@ -14,8 +14,9 @@ dominant kernel against the HBM roofline (8 TB/s), the CPU oracle on the
 host (which also checks every element of every case's GPU output), the
 leading-dimension, awkward and literal shapes, the 512-problem batch, the
 served trace, the complex, mixed-precision and packing cases, and three
-tensor contractions by transpose-transpose-GEMM-transpose (whole, panel
-GEMM alone, and torch's tensordot on the same tensors).  The printed JSON
+tensor contractions (each against the matrix cores' peak and the bytes it
+cannot do without, with the panel GEMM of its extents and torch's tensordot
+on the same tensors beside it).  The printed JSON
 line holds the summary; the per-case detail goes to ``--detail-out``.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W]
@@ -42,7 +43,7 @@ SLOTS = 8
 TRAFFIC = os.path.join(ROOT, "profiles", "traffic_counters.json")
 # the per-call kernels' sources (their code, without comments, keys the counter traffic)
 KERNEL_SOURCES = (["device_types.h", "tile_kernels.h", "menu.h", "registry.h", "moved_launch.h",
-                   "staged_launch.h", "dispatch.hip", "jit.cpp"] +
+                   "staged_launch.h", "dispatch.hip", "jit.cpp", "box.h", "box_kernel.h"] +
                   sorted(os.path.basename(f) for f in glob.glob(os.path.join(
                       os.path.dirname(os.path.abspath(__file__)), "paper_1607_01249_amd", "csrc",
                       "kernels_*.hip"))))
@@ -93,7 +94,7 @@ def parse_args():
     ap.add_argument("--no-types", action="store_true",
                     help="skip the complex (c, z) and mixed-precision (sd, ds, cz, zc) cases")
     ap.add_argument("--no-contraction", action="store_true",
-                    help="skip the transpose-transpose-GEMM-transpose contractions")
+                    help="skip the tensor contractions")
     ap.add_argument("--only-contraction", action="store_true",
                     help="for rocprofv3: only the contractions (after the ceilings), then exit")
     ap.add_argument("--serve-seconds", type=float, default=10.0)
@@ -675,11 +676,12 @@ def bench_packing(torch, ttx, d2d, stream, tune_candidates, reps=10):
 
 
 def bench_contraction(torch, ttx, d2d, stream, reps=10):
-    """Transpose-transpose-GEMM-transpose contractions (the workloads'
-    CONTRACTIONS), operands resident: the whole ttx_contraction_execute, its
-    panel GEMM alone (ttx_gemm_panels on panels of the same extents), the
-    rest (transpositions and packing) as the difference, and torch's
-    tensordot on the same tensors as a point of comparison."""
+    """Tensor contractions (the workloads' CONTRACTIONS), operands resident:
+    ttx_contraction_execute against the matrix cores' peak and against the
+    bytes it cannot do without (A, B and C once, C twice where beta != 0).
+    Beside it the panel GEMM of the same extents on packed operands
+    (ttx_gemm_panels, which contractions do not run) and torch's tensordot on
+    the same tensors."""
     import workloads
     out = []
     for case in workloads.CONTRACTIONS:
@@ -736,22 +738,17 @@ def bench_contraction(torch, ttx, d2d, stream, reps=10):
         torch_ttgt()
         _, t_torch = time_events(torch, torch_ttgt, reps)
         flops = 2.0 * m * n * k
-        rest_bytes = es * ((2 * m * k if info["transposed_a"] else 0) + (2 * k * n if info["transposed_b"] else 0)
-                           + m * k + -(-m // panel) * panel * K + k * n + -(-n // panel) * panel * K
-                           + m * n * (3 if case["beta"] != 0 else 2))
-        t_rest = max(t_all - t_gemm, 1e-9)
+        nbytes = es * (m * k + k * n + m * n * (2 if case["beta"] != 0 else 1))
         peak = 157.3 if code == ttx.F32 else 78.6
-        out.append(dict(case=case["name"], m=m, n=n, k=k, panel=panel, transposed_a=info["transposed_a"],
-                        transposed_b=info["transposed_b"], ms=round(t_all * 1e3, 3),
-                        TFLOPs=round(flops / t_all / 1e12, 2), gemm_ms=round(t_gemm * 1e3, 3),
-                        gemm_TFLOPs=round(flops / t_gemm / 1e12, 2), gemm_frac_of_peak=round(flops / t_gemm / 1e12 / peak, 3),
-                        rest_ms=round(t_rest * 1e3, 3), rest_bytes=rest_bytes,
-                        rest_GBps=round(rest_bytes / t_rest / 1e9, 1),
-                        rest_pct_of_d2d=round(100 * rest_bytes / t_rest / 1e9 / d2d, 1) if d2d else None,
-                        torch_tensordot_ms=round(t_torch * 1e3, 3),
-                        x_torch=round(t_torch / t_all, 2)))
-        log("  %s: %.3f ms (GEMM %.3f ms = %.1f TFLOP/s; rest %.3f ms) vs torch %.3f ms" % (
-            case["name"], t_all * 1e3, t_gemm * 1e3, flops / t_gemm / 1e12, t_rest * 1e3, t_torch * 1e3))
+        gbps = nbytes / t_all / 1e9
+        out.append(dict(case=case["name"], m=m, n=n, k=k, ms=round(t_all * 1e3, 3),
+                        TFLOPs=round(flops / t_all / 1e12, 2), gemm_frac_of_peak=round(flops / t_all / 1e12 / peak, 3),
+                        bytes=nbytes, GBps=round(gbps, 1), pct_of_d2d=round(100 * gbps / d2d, 1) if d2d else None,
+                        panel=panel, panel_gemm_ms=round(t_gemm * 1e3, 3),
+                        panel_gemm_TFLOPs=round(flops / t_gemm / 1e12, 2),
+                        torch_tensordot_ms=round(t_torch * 1e3, 3), x_torch=round(t_torch / t_all, 2)))
+        log("  %s: %.3f ms = %.1f TFLOP/s, %.0f GB/s (panel GEMM alone %.3f ms) vs torch %.3f ms" % (
+            case["name"], t_all * 1e3, flops / t_all / 1e12, gbps, t_gemm * 1e3, t_torch * 1e3))
         del T, ws
         torch.cuda.empty_cache()
     return out
@@ -1229,7 +1226,7 @@ def main():
         packing = bench_packing(torch, ttx, d2d, stream, args.tune_candidates)
     contraction = None
     if not args.no_contraction and not args.profile_run:
-        log("tensor contractions (transpose-transpose-GEMM-transpose)")
+        log("tensor contractions")
         contraction = bench_contraction(torch, ttx, d2d, stream)
     if args.save_table:
         ttx.ttx_tune_table_save(args.save_table)
