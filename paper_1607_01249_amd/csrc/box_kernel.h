@@ -2,8 +2,9 @@
 //
 // Large problems are bound by memory: whole runs on both sides reach 5.5 TB/s
 // (6D f64 [20,16,16,20,16,16], update, 0.117 ms; the whole-unit dense tiles
-// took 0.175) and short or unaligned ones 4.6 to 5.4 (4D f32 reversal 0.089 ms,
-// 6D f32 reversal with odd extents 0.136), where a copy runs at 6.1.  Small ones
+// took 0.175) and short or unaligned ones 4.6 to 5.4 (4D f32 reversal 0.080 ms
+// with nontemporal stores, 6D f32 reversal with odd extents 0.136), where a copy
+// runs at 6.1.  Small ones
 // are bound by one box's chain: arguments, offsets, loads, LDS, stores.  The
 // offsets were the bound at first: with integer divisions and one pass of the
 // indices per unit a box cost 1000 instructions and 80 scalar loads one after

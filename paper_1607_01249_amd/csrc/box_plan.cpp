@@ -327,7 +327,7 @@ bool make_box(const Problem& p, bool beta0, const Box& b, BoxPlan* out) {
     out->units = small_box(p, b) ? 2 : 4;
     // Nontemporal stores where B is only written, in whole lines, and is a good
     // part of the 256 MiB that the last cache holds: 0.74 to 0.95 of the time on
-    // five such problems (4D f32 reversal 88.9 -> 79.7 us).  With partial lines
+    // six such problems (4D f32 reversal 89.4 -> 80.6 us).  With partial lines
     // they took up to 1.5 times as long, below 8 us 1.04, with beta != 0 the same.
     out->nt = beta0 && whole_lines_b(p, b) && p.extent_b >= int64_t(64) << 20;
     s.tA = sa >= 0 ? int(t[sa]) : 1;

@@ -292,11 +292,12 @@ void plan_contraction_as(int dtype, const ContractLabel* labels, int count, int 
 
 // The tile shape, splits and packing with the least estimated time: matrix or
 // address cycles of the CU with the most tiles (a last wave that fills a few
-// CUs costs as much as a full one, which is why the menu holds 80 columns: m =
-// n = k = 1600 FP32 takes 82 us with 64 x 80 tiles, two a CU, 92 with 64 x 64
-// and 110 with 128 x 64), or the latency of the k steps where few workgroups
-// run (128 x 96 results, k = 2048: 16 us in 16 splits, 69 in one), or C's
-// traffic.  Packing the operands of a short sum costs a launch and pays where
+// CUs costs as much as a full one, which is what 80 columns are for), or the
+// latency of the k steps where few workgroups run (128 x 96 results, k = 2048:
+// 16 us in 16 splits, 69 in one), or C's traffic.  80 columns were taken for 46
+// of 153 FP32 products and contractions of long sums; without that shape those
+// take 1.06 times as long (0.81 to 1.58; m = n = k = 1600: 88 us against 79).
+// In FP64 the 48 that take it would do as well without (0.997; 0.86 to 1.34).  Packing the operands of a short sum costs a launch and pays where
 // many tiles read them in short runs (24^6 FP32 results, sums of 16: 309 us
 // against 326; with beta = 0 150 against 212).  Over 25 shapes in both types
 // the choice was within 10% of the best of the menu on 22.
