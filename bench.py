@@ -436,8 +436,8 @@ def _pct(v, q):
 
 
 def bench_batched(torch, ttx, reps=20, tune=True):
-    """The 512 uneven transpositions: per-call loop vs one graph-captured
-    persistent launch (after per-shape tuning)."""
+    """The 512 uneven transpositions: per-call loop vs the batch as one graph
+    replay (after per-shape tuning)."""
     import workloads
     probs = workloads.batched_problems()
     stream = torch.cuda.current_stream().cuda_stream
@@ -500,7 +500,7 @@ def bench_batched(torch, ttx, reps=20, tune=True):
                              makespan_p99_ms=round(_pct(times, 99) * 1e3, 3),
                              grid=info["grid"], tiles=info["total_tiles"], chunks=info["chunks"],
                              variants=info["variants_used"], tuned=info["tuned"],
-                             tune_seconds=round(tune_s, 1), launch="1 persistent kernel per hipGraph replay"),
+                             tune_seconds=round(tune_s, 1), launch="one hipGraph replay: the boxes of all problems in one kernel"),
                 speedup=round(pc_med / b_med, 2))
 
 

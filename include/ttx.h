@@ -272,17 +272,18 @@ ttx_status ttx_plan_kernel_name(const ttx_plan *plan, double beta, const void *A
  * box tiles is compiled (see ttx_transpose; "ttx_jit_..._box..."), where it
  * has them; the plan's config is then what it runs without that kernel.
  *   reps == 0: the kernel is attached to the plan;
- *   reps > 0:  the generic and the specialised kernel are timed on scratch
- *              tensors the call allocates (minimum of `reps` runs each,
- *              caches flushed before each run, as ttx_tune does), and the
- *              specialised kernel is attached only when it is more than 1%
- *              faster (stage 5 of Sec. 2.1 over the two variants).
+ *   reps > 0:  the generic kernel and the specialised ones (of the tiles of
+ *              the config and, where they are compiled, of the box tiles) are
+ *              timed on scratch tensors the call allocates (minimum of `reps`
+ *              runs each, caches flushed before each run, as ttx_tune does),
+ *              and the fastest specialised kernel is attached only when it is
+ *              more than 1% faster (stage 5 of Sec. 2.1 over the variants).
  * *kept (may be NULL) receives 1 when a kernel was attached.  Later
  * executions of the plan in that beta class, on that device, launch it
  * when the tensors are aligned as for the plan's vector paths (16 bytes
  * suffices; hipMalloc'd tensors are; kernels of box tiles take any alignment);
- * other executions use the generic kernel.  Both compute the same bits.  Moved- and preserved-family
- * problems only: for empty and single-index problems nothing is attached
+ * other executions use the generic kernel.  Both compute the same bits.
+ * Moved- and preserved-family problems only: for empty and single-index problems nothing is attached
  * (TTX_OK, no GPU call).  A call replaces the plan's earlier specialised
  * kernel of that beta class; ttx_plan_set_config drops it.  Kernels stay
  * loaded until the process ends and are shared by plans of the same
@@ -583,7 +584,8 @@ ttx_status ttx_batch_execute(ttx_batch *batch, hipStream_t stream);
 /* The same kernels launched directly (no graph). */
 ttx_status ttx_batch_execute_direct(ttx_batch *batch, hipStream_t stream);
 /* New pointers and scalars for problems of unchanged shape; the copy to the
- * descriptor table is ordered on `stream` and completes before returning. */
+ * descriptor table is ordered on `stream` and completes before returning.
+ * Allocates no device memory. */
 ttx_status ttx_batch_update(ttx_batch *batch, int count, const ttx_problem *problems,
                             hipStream_t stream);
 ttx_status ttx_batch_get_info(const ttx_batch *batch, ttx_batch_info *info);

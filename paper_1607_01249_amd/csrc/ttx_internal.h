@@ -243,7 +243,8 @@ bool jit_matches(const JitKernel& k, const TiledLaunch& L);
 // The kernel's name as profilers print it.
 const std::string& jit_name(const JitKernel& k);
 hipError_t jit_launch(const JitKernel& k, const TiledLaunch& L, hipStream_t stream);
-// The same for a box kernel (for pointers of any alignment).
+// The same for a box kernel (for pointers of any alignment: where the box has
+// nontemporal stores, the kernel holds both kinds and chooses by B's address).
 struct BoxPlan;
 ttx_status jit_box_kernel(const Problem& p, const BoxPlan& bp, bool beta0, const JitKernel** out);
 std::string jit_box_source(const Problem& p, const BoxPlan& bp, bool beta0);
