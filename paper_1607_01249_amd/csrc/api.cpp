@@ -456,7 +456,7 @@ ttx_status ttx_plan_kernel_name(const ttx_plan* plan, double beta, const void* A
     std::string name;
     TiledLaunch L;
     if (x->jit && x->box && jit_on_device(*x->jit))
-        name = jit_name(*x->jit);
+        name = jit_box_name(*x->jit, B);
     else if (x->jit && !x->box &&
              prepare_tiled(p, x->cfg, beta0, A, B, const_cast<void*>(B), Scalar(1.0), Scalar(beta), &L) &&
              jit_matches(*x->jit, L))

@@ -26,7 +26,7 @@ constexpr int kBoxUnits = 4;    // most units per thread and side
 
 // Whether B starts on a 128-byte line.  Nontemporal stores of partial lines
 // are slow, and a B that does not has them throughout.
-__host__ __device__ __forceinline__ bool box_on_line(const void* B) { return (unsigned long long)(B) % 128 == 0; }
+inline bool box_on_line(const void* B) { return (unsigned long long)(B) % 128 == 0; }
 
 struct BoxDim {
     int ext;         // extent in the box

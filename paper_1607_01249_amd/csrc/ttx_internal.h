@@ -244,11 +244,12 @@ bool jit_matches(const JitKernel& k, const TiledLaunch& L);
 const std::string& jit_name(const JitKernel& k);
 hipError_t jit_launch(const JitKernel& k, const TiledLaunch& L, hipStream_t stream);
 // The same for a box kernel (for pointers of any alignment: where the box has
-// nontemporal stores, the kernel holds both kinds and chooses by B's address).
+// nontemporal stores, a second kernel serves a B off a line).
 struct BoxPlan;
 ttx_status jit_box_kernel(const Problem& p, const BoxPlan& bp, bool beta0, const JitKernel** out);
 std::string jit_box_source(const Problem& p, const BoxPlan& bp, bool beta0);
 bool jit_on_device(const JitKernel& k);   // loaded on the current device
+std::string jit_box_name(const JitKernel& k, const void* B);
 hipError_t jit_box_launch(const JitKernel& k, const Problem& p, const BoxPlan& bp, const void* A, const void* Bsrc,
                           void* Bdst, const Scalar& alpha, const Scalar& beta, hipStream_t stream);
 // C++ spelling of an element type ("float", "ttx::cf32", "ttx::f32x4", ...).
